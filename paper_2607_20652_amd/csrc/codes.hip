@@ -26,7 +26,8 @@
 // readlane, and matrix-core fragments are fetched in batches.
 #include <algorithm>
 
-#include "scoring.hpp"
+#include "backward.hpp"
+#include "columns.hpp"
 
 namespace dpb {
 namespace {
@@ -36,41 +37,7 @@ constexpr int kBatch = 16;    // leaf columns decoded per batch
 constexpr int kBwdBatch = 4;
 constexpr int kDecodeUnroll = 4;  // coordinates of the table decode whose reads are issued together
 
-struct Wave {
-    int lane;
-    int64_t t0;
-    int ntok;
-    int32_t* idx;     // [TPW][k]
-    float* coef;      // [TPW][k]
-    int32_t* route;   // [TPW][k]: (parent slot << 16) | j (| kClaimed when decoded by its column), or -1
-    int32_t* par;     // [16] parent index of each column row
-    float* alpha;     // [16][dpad] column coefficients
-    int32_t* claim;   // [16][dpad] lowest slot claiming (row, j)
-    int32_t* fri;     // [fr_cap] indices of the table-decoded slots
-    float* frc;       // [fr_cap] their coefficients (0 for basis and padding slots)
-    uint32_t* frv;    // [fr_cap / 32][8][16] slot-parity tables (256-byte aligned)
-    float* frt;       // [fr_cap / 4][16] signed coefficient sums
-    void* pb;         // [TPW][dp] sign bits of the leaf level's parents (pb_bytes each)
-    float* y;         // [TPW][dp] output accumulator (fp32)
-    uint32_t* pairs;  // [TPW][prow] g as signed bf16 pairs, interleaved halves
-    float* gf;        // [TPW][dp] fp32 g (fp32 activations)
-    uint32_t* cw;     // [16][cws] column sign bitmaps
-    float* score;     // [16][16] scores of one column block and generator tile
-    const uint32_t* mask;  // [dp] row masks (shared)
-    const uint32_t* gtab;  // generator hash tables (shared): (g_j, j) pairs
-    const uint32_t* gens;  // generators (shared)
-};
-
 __device__ __forceinline__ int rdlane(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
-
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-typedef __attribute__((address_space(3))) float lds_f32;
-__device__ __forceinline__ uint32_t lds_addr(const void* p)
-{
-    return (uint32_t)(size_t)(const __attribute__((address_space(3))) void*)p;
-}
-__device__ __forceinline__ uint32_t lds_ld(uint32_t a) { return *(const lds_u32*)(size_t)a; }
-__device__ __forceinline__ float lds_ldf(uint32_t a) { return *(const lds_f32*)(size_t)a; }
 
 // Routes every hashed slot of the last level: finds the first parent slot q
 // of the previous level (in slot order) and the generator j with
@@ -114,25 +81,6 @@ __device__ void route_slots(const DevPlan& P, const Wave& W)
     }
 }
 
-// Bit transpose inside each 32-lane half: lane s of a half holds x_s on
-// entry; on exit lane b holds the word whose bit s is bit b of x_s.  The five
-// exchanges run on the vector ALU (a chain of LDS-path swizzles was slower).
-__device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane)
-{
-    uint32_t o;
-    o = lane_xor<16>(x);
-    x = (lane & 16) ? ((x & 0xFFFF0000u) | ((o >> 16) & 0x0000FFFFu)) : ((x & 0x0000FFFFu) | ((o & 0x0000FFFFu) << 16));
-    o = lane_xor<8>(x);
-    x = (lane & 8) ? ((x & 0xFF00FF00u) | ((o >> 8) & 0x00FF00FFu)) : ((x & 0x00FF00FFu) | ((o & 0x00FF00FFu) << 8));
-    o = lane_xor<4>(x);
-    x = (lane & 4) ? ((x & 0xF0F0F0F0u) | ((o >> 4) & 0x0F0F0F0Fu)) : ((x & 0x0F0F0F0Fu) | ((o & 0x0F0F0F0Fu) << 4));
-    o = lane_xor<2>(x);
-    x = (lane & 2) ? ((x & 0xCCCCCCCCu) | ((o >> 2) & 0x33333333u)) : ((x & 0x33333333u) | ((o & 0x33333333u) << 2));
-    o = lane_xor<1>(x);
-    x = (lane & 1) ? ((x & 0xAAAAAAAAu) | ((o >> 1) & 0x55555555u)) : ((x & 0x55555555u) | ((o & 0x55555555u) << 1));
-    return x;
-}
-
 template <int NG, int LG, bool PB16>
 __device__ __forceinline__ void fr_coords(const DevPlan& P, const Wave& W, int tt, int Wn, bool first, int pbpos, int pbn);
 template <int NG, int LG, bool PB16, int FRU>
@@ -152,7 +100,7 @@ __device__ __forceinline__ void fr_coords1(const DevPlan& P, const Wave& W, int 
 template <int NG, bool PB16, int FRU>
 __device__ void fr_chunk(const DevPlan& P, const Wave& W, int tt, int n, bool first, int pbpos, int pbn)
 {
-    const int lane = W.lane, dp = P.dp;
+    const int lane = W.lane;
     const int Wn = (n + 31) >> 5;
     // slot-parity tables: frv[w][g][v] = bits over the slots of word w of parity(idx & (v << 4g))
     for (int h = 0; 64 * h < n; ++h) {
@@ -761,153 +709,6 @@ __global__ __launch_bounds__(kThreads) void decode2_kernel(DevPlan P, const int3
     }
 }
 
-// g at coordinate iota of token tt, from the LDS copy.
-template <bool G_BF16>
-__device__ __forceinline__ float g_at(const DevPlan& P, const Wave& W, int tt, int iota)
-{
-    if constexpr (G_BF16) return pair_value(P, W.pairs, tt, iota);
-    else return W.gf[tt * P.dp + iota];
-}
-
-// Child scores of the parent columns of level l against the wave's g,
-// written to the coefficients of the slots routed to them.
-template <bool G_BF16>
-__device__ void score_level(const DevPlan& P, const Wave& W, int l)
-{
-    const int k = P.k_tot, TPW = P.wave_tokens, lane = W.lane;
-    const int CPT = P.cpt[l], csh = P.cpt_shift[l], Kp = P.active[l - 1], Kl = P.active[l];
-    const int ncol = TPW * CPT, NB = (ncol + 15) >> 4, sbp = P.slot_base[l - 1], sbl = P.slot_base[l];
-    const ActTile A{W.pairs, W.gf};
-    const int col = lane & 15, kq = lane >> 4;
-    for (int nb = 0; nb < NB; ++nb) {
-        column_bitmaps(P, lane, W.ntok, csh, nb, W.idx + sbp, k, Kp, P.nt, W.cw);
-        wave_sync();
-        const int r = nb * 16 + col, tt = r >> csh, q = r & (CPT - 1);
-        const bool valid = r < ncol && tt < W.ntok && q < Kp && W.idx[tt * k + sbp + q] >= 0;
-        const int trow = valid ? tt : 0;
-        for (int mb = 0; mb < P.mblocks[l]; ++mb) {
-            const f32x4 acc = mfma_scores<G_BF16>(P, lane, l, mb, trow, A, W.cw);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) W.score[col * 16 + kq * 4 + i] = acc[i] * P.rsd;
-            wave_sync();
-            // slots routed to a column of this block and a generator of this tile
-            for (int tt2 = 0; tt2 < W.ntok; ++tt2)
-                for (int s = sbl + lane; s < sbl + Kl; s += 64) {
-                    const int rt = W.route[tt2 * k + s];
-                    if (rt < 0) continue;
-                    const int r2 = (tt2 << csh) + (rt >> 16), j = rt & 0xFFFF;
-                    if ((r2 >> 4) == nb && (j >> 4) == mb) W.coef[tt2 * k + s] = W.score[(r2 & 15) * 16 + (j & 15)];
-                }
-            wave_sync();
-        }
-    }
-}
-
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-
-// c + a.lo b.lo + a.hi b.hi for bf16 pairs.  The operands are taken as plain
-// words: a bit cast of a vector element (pq.y) reads element 0 with this
-// compiler.
-__device__ __forceinline__ float dot2u(uint32_t a, uint32_t b, float c)
-{
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, a), __builtin_bit_cast(bf16x2v, b), c, false);
-}
-
-// +-1 bf16 pair carrying bits 15 and 31 of R as its signs
-__device__ __forceinline__ uint32_t unit_pair(uint32_t R)
-{
-    return __builtin_amdgcn_bitop3_b32(R, 0x80008000u, 0x3F803F80u, 0xEA);   // (R & signs) | one
-}
-
-// grad_coef of the hashed slots that route nowhere: the scaled sum over the
-// coordinates of g(iota) (-1)^{parity(M_iota & c)} for slot index c, with
-// one lane per slot while 64 or more remain, then 2, 4 or 8 lanes per slot
-// (each taking every 2nd, 4th or 8th chunk) in rounds of 32, 16 and 8 slots,
-// so that the lanes stay busy (48 slots: 32 at two lanes, then 16 at four,
-// 18 chunk steps instead of 24).  The slot's signs over the 32
-// coordinates of chunk w form one word, the XOR of one nibble-table word per
-// 4-bit group of c (parity is linear in the index bits).  bf16 g: dword o of
-// the chunk holds coordinates o and o + 16, which meet the +-1 pair made from
-// word bits o and o + 16 in a two-element dot product (fp32 accumulation).
-template <bool G_BF16, int NG>
-__device__ void direct_scores(const DevPlan& P, const Wave& W)
-{
-    static_assert(NG <= kNtGroupsPadded, "nibble groups beyond the padded tables");
-    const int k = P.k_tot, n = W.ntok * k, lane = W.lane, nchunk = P.nchunk, d = P.d;
-    int32_t* list = (int32_t*)W.score;   // 256 entries
-    const uint64_t below = (1ull << lane) - 1;
-    for (int w0 = 0; w0 < n; w0 += 256) {
-        int m = 0;
-        for (int b = w0; b < min(n, w0 + 256); b += 64) {
-            const int i = b + lane;
-            const bool act = i < n && W.idx[i] >= d && W.route[i] < 0;
-            const uint64_t bal = __ballot(act);
-            if (act) list[m + __popcll(bal & below)] = i;
-            m += __popcll(bal);
-        }
-        wave_sync();
-        for (int r0 = 0; r0 < m;) {
-            const int rem = m - r0;
-            const int sh = rem >= 64 ? 0 : rem >= 32 ? 1 : rem >= 16 ? 2 : 3;   // 2^sh lanes per slot
-            const int mr = min(64 >> sh, rem);
-            const int r = lane & ((64 >> sh) - 1), part = lane >> (6 - sh);
-            const bool valid = r < mr;
-            const int item = list[r0 + (valid ? r : 0)];
-            const int tt = item / k;
-            const uint32_t c = (uint32_t)W.idx[item];
-            float acc0 = 0.f, acc1 = 0.f;
-            // the nibble-table words of the next chunk are requested before
-            // this chunk is summed (the device tables hold at least NG groups,
-            // zero words past nt_groups)
-            uint32_t toff[NG], tw[NG];
-#pragma unroll
-            for (int g = 0; g < NG; ++g) toff[g] = 4u * ((uint32_t)(g * nchunk * 16) + ((c >> (4 * g)) & 15u));
-            const unsigned char* ntb = (const unsigned char*)P.nt;   // byte offsets: 32-bit address arithmetic
-            auto fetch_words = [&](int w) {
-#pragma unroll
-                for (int g = 0; g < NG; ++g) tw[g] = *(const uint32_t*)(ntb + (toff[g] + (uint32_t)(w * 64)));
-            };
-            auto fold_words = [&]() {
-                uint32_t v = 0;
-#pragma unroll
-                for (int g = 0; g < NG; ++g) v ^= tw[g];
-                return v;
-            };
-            fetch_words(min(part, nchunk - 1));
-            for (int w = part; w < nchunk; w += 1 << sh) {
-                const uint32_t word = fold_words();
-                fetch_words(min(w + (1 << sh), nchunk - 1));
-                // keeps the compiler from sinking those loads to their use
-                __asm__ volatile("" ::: "memory");
-                if constexpr (G_BF16) {
-                    const u32x4* pr = (const u32x4*)(W.pairs + tt * P.prow + w * 16);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const u32x4 pq = pr[q];
-                        const int o = 4 * q;
-                        acc0 = dot2u(pq.x, unit_pair(word << (15 - o)), acc0);
-                        acc1 = dot2u(pq.y, unit_pair(word << (14 - o)), acc1);
-                        acc0 = dot2u(pq.z, unit_pair(word << (13 - o)), acc0);
-                        acc1 = dot2u(pq.w, unit_pair(word << (12 - o)), acc1);
-                    }
-                } else {
-                    const float* gr = W.gf + tt * P.dp + 32 * w;
-#pragma unroll
-                    for (int b = 0; b < 32; b += 2) {
-                        acc0 += __uint_as_float(__float_as_uint(gr[b]) ^ ((word << (31 - b)) & 0x80000000u));
-                        acc1 += __uint_as_float(__float_as_uint(gr[b + 1]) ^ ((word << (30 - b)) & 0x80000000u));
-                    }
-                }
-            }
-            float acc = acc0 + acc1;
-            for (int off = 64 >> sh; off < 64; off <<= 1) acc += __shfl_xor(acc, off, 64);
-            if (valid && part == 0) W.coef[item] = P.rsd * acc;
-            r0 += mr;
-        }
-        wave_sync();   // the list is rewritten by the next window
-    }
-}
-
 // PF1: the next group's code is prefetched for waves of one token (a
 // separate instance: selecting the layout at run time costs the two-token
 // form a wave per SIMD in registers).
@@ -1020,19 +821,6 @@ size_t code_lds_bytes(const DevPlan& P, bool scoring, bool act_bf16)
     return code_shared_bytes(P) + (size_t)kCodeWaves * code_layout(P, scoring, act_bf16).bytes;
 }
 
-int device_cus()
-{
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            cus = prop.multiProcessorCount;
-        if (cus <= 0) cus = 256;
-    }
-    return cus;
-}
-
 // Grid-stride launch: `rounds` times the workgroups the chip holds at once
 // (measured best: one round for the decode, four for the backward).
 dim3 code_grid(const DevPlan& P, int64_t T, size_t lds, int rounds)
@@ -1069,14 +857,6 @@ bool code_kernels_fit(const DevPlan& P)
     return code_rows_fit(code_plan(P));
 }
 
-// Kernel variants: index groups NG in {3, 4, 5, 6, 8} (a larger NG than the
-// plan needs is exact: the extra table rows are zero) and the width of the
-// leaf parents' sign bits.
-int ng_variant(const DevPlan& P)
-{
-    return P.nt_groups <= 3 ? 3 : P.nt_groups <= 6 ? P.nt_groups : 8;
-}
-
 template <bool OB, int NG, bool PB>
 static void launch_decode_v(const DevPlan& P, dim3 grid, size_t lds, hipStream_t stream, const int32_t* idx,
                             const float* coef, int64_t T, void* y)
@@ -1101,6 +881,7 @@ static void launch_decode_ng(const DevPlan& P, dim3 grid, size_t lds, hipStream_
 hipError_t launch_decode2(const DevPlan& Pp, const int32_t* idx, const float* coef, int64_t T, void* y, bool y_bf16,
                           hipStream_t stream)
 {
+    if (launch_col_decode(Pp, idx, coef, T, y, y_bf16, stream)) return hipGetLastError();
     const DevPlan P = code_plan(Pp);
     const size_t lds = code_lds_bytes(P, false, true);
     if (lds > (size_t)kLdsBudget) return hipErrorInvalidValue;
@@ -1112,12 +893,6 @@ hipError_t launch_decode2(const DevPlan& Pp, const int32_t* idx, const float* co
     else launch_decode_ng<false, false>(P, grid, lds, stream, idx, coef, T, y);
     return hipGetLastError();
 }
-
-struct BwdExtra {
-    const float* gc;
-    const void* gx;
-    const float2* stats;
-};
 
 template <bool GB, bool XB, int NG, bool PB>
 static void launch_bwd_v(const DevPlan& P, dim3 grid, size_t lds, hipStream_t stream, const int32_t* idx,
@@ -1161,11 +936,12 @@ hipError_t launch_decode_bwd2(const DevPlan& Pp, const int32_t* idx, const void*
                               float* grad_coef, void* grad_x, bool gx_bf16, hipStream_t stream,
                               const float* add_grad_coef, const void* add_grad_x, const float* stats)
 {
+    const BwdExtra ex{add_grad_coef, add_grad_x, (const float2*)stats};
+    if (launch_col_bwd(Pp, idx, g, g_bf16, T, grad_coef, grad_x, gx_bf16, ex, stream)) return hipGetLastError();
     const DevPlan P = code_plan(Pp);
     const size_t lds = code_lds_bytes(P, true, g_bf16);
     if (lds > (size_t)kLdsBudget) return hipErrorInvalidValue;
     const dim3 grid = code_grid(P, T, lds, 4);
-    const BwdExtra ex{add_grad_coef, add_grad_x, (const float2*)stats};
     if (g_bf16 && gx_bf16) launch_bwd_ub<true, true>(P, grid, lds, stream, idx, g, T, grad_coef, grad_x, ex);
     else if (g_bf16) launch_bwd_ub<true, false>(P, grid, lds, stream, idx, g, T, grad_coef, grad_x, ex);
     else if (gx_bf16) launch_bwd_ub<false, true>(P, grid, lds, stream, idx, g, T, grad_coef, grad_x, ex);

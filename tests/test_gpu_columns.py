@@ -1,0 +1,109 @@
+"""GPU parity of the column decode and its backward (columns.hpp) where they
+can go wrong: each number of parent columns per token, widths that fill no
+coordinate step or no pair, parents that are basis features, several words of
+summed slots, and codes the encoder does not produce (a slot that routes to no
+parent, repeated indices, hashed indices on level 0, padding, indices drawn at
+random).  `wide_code` has more slots than a mark byte holds and takes the
+table decode instead.
+"""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2607_20652_amd import binding as dpb
+from paper_2607_20652_amd import inputs
+from parity_util import TOL_BF16, TOL_F32, compare_dense
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+# name: (d, level bits, K per level); 16 children per parent
+PLANS = {
+    "cpt8": (768, (10, 12, 15, 17, 20), (8, 8, 8, 8, 64)),
+    "cpt4_d200": (200, (8, 10, 12), (4, 4, 8)),
+    "cpt16": (1024, (10, 12, 15, 18, 21, 24), (16, 16, 16, 16, 16, 64)),
+    "odd_d": (101, (7, 10, 13), (8, 8, 24)),
+    "d_tail": (1000, (10, 13, 16, 18), (6, 5, 6, 20)),       # 6 parents of 8 columns, 5 summed slots
+    "basis_parents": (256, (8, 12), (8, 32)),
+    "one_step": (40, (6, 9, 12), (16, 16, 48)),              # dp = 64 < one step of 128 coordinates
+    "many_words": (512, (9, 11, 13, 15, 17, 19, 21, 23), (12, 12, 12, 12, 12, 12, 9, 18)),
+    "beam24": (384, (9, 12, 15, 18), (24, 24, 8, 32)),       # 24 summed slots: all six groups of word 0
+    "wide_code": (768, (10, 14, 18), (16, 16, 256)),
+}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    dpb.load()
+
+
+def codes(name, T, seed):
+    """Codes of random children (the layout of the encoder's), then one oddity per row."""
+    d, nb, K = PLANS[name]
+    L, rng = len(nb), np.random.default_rng(seed)
+    dl = [0] + [16] * (L - 1)
+    gens = oracle.generators(list(nb), dl, 0)
+    base = np.concatenate([[0], np.cumsum(K)]).astype(int)
+    idx = np.full((T, sum(K)), -1, np.int32)
+    for t in range(T):
+        par = rng.choice(d, K[0], replace=False)
+        idx[t, : K[0]] = par
+        for l in range(1, L):
+            g = np.asarray(gens[l], np.int64)
+            child = rng.permutation(np.unique(par[:, None] ^ g[None, :]))[: K[l]]
+            idx[t, base[l]:base[l] + len(child)] = child
+            par = child
+    coef = rng.standard_normal(idx.shape).astype(np.float32)
+    coef[idx < 0] = 0.0
+    k, N = sum(K), 1 << nb[-1]
+    rand = lambda: int(rng.integers(d, N))
+    odd = {
+        1: lambda r: r.__setitem__(k - 1, rand()),                            # routes to no parent
+        2: lambda r: r.__setitem__(1, r[0]),                                  # a basis slot twice
+        3: lambda r: r.__setitem__(slice(base[L - 1], k), r[base[L - 1]]),    # one leaf in every leaf slot
+        4: lambda r: r.__setitem__(0, r[k - 1]),                              # a hashed index on level 0
+        5: lambda r: r.__setitem__(k - 1, r[0]),                              # a basis index among the leaves
+        6: lambda r: r.__setitem__(base[L - 2], rand() if L > 2 else r[1]),   # another parent: its children route nowhere
+        7: lambda r: r.__setitem__(slice(0, k), -1),                          # all padding
+        8: lambda r: r.__setitem__(slice(0, k), rng.integers(0, N, k)),       # any indices
+        9: lambda r: r.__setitem__(slice(base[L - 2], base[L - 2] + 2), -1),  # padding parents
+        10: lambda r: r.__setitem__(slice(0, k), rng.integers(0, d, k)),      # basis indices everywhere, repeated
+    }
+    for t, f in odd.items():
+        f(idx[t])
+    coef[idx < 0] = 0.0
+    return idx, coef
+
+
+@pytest.mark.parametrize("name", list(PLANS))
+def test_column_decode_and_bwd(name):
+    d, nb, K = PLANS[name]
+    T = 23                                       # ragged last group for 2 and 4 tokens per wave
+    print(f"[columns] {name} d={d} T={T}", flush=True)
+    sys.stdout.flush()
+    plan = dpb.Plan(d, seed=0, level_bits=list(nb), branchings=[0] + [16] * (len(nb) - 1), active=list(K))
+    m = oracle.masks(d, nb[-1])
+    idx, coef = codes(name, T, 9000 + d)
+    di, dc = torch.from_numpy(idx).to(DEV), torch.from_numpy(coef).to(DEV)
+    ref = oracle.decode(d, m, idx, coef.astype(np.float64))
+    for dt, tol in ((torch.float32, TOL_F32), (torch.bfloat16, TOL_BF16)):
+        y = dpb.decode(plan, di, dc, dt)
+        compare_dense(y.float().cpu().numpy(), ref, tol)
+    for dt in ("f32", "bf16"):
+        g = inputs.normal((T, d), 9100 + d, dt)
+        rgc, rgx = oracle.decode_bwd(d, m, idx, g.double().numpy())
+        for xt, tol in ((torch.float32, TOL_F32), (torch.bfloat16, TOL_BF16)):
+            gc, gx = dpb.decode_bwd(plan, di, g.to(DEV), gx_dtype=xt)
+            compare_dense(gc.cpu().numpy(), rgc, TOL_F32)
+            compare_dense(gx.float().cpu().numpy(), rgx, tol)
+            # the extra term added in place (the layer's use): same rows plus add
+            add = inputs.normal((T, d), 9200 + d, "f32").to(xt)
+            buf = add.to(DEV)
+            _, gx2 = dpb.decode_bwd_ex(plan, di, g.to(DEV), add_grad_x=buf, grad_x=buf)
+            compare_dense(gx2.float().cpu().numpy(), rgx + add.double().numpy(), tol)
