@@ -15,6 +15,85 @@ __host__ __device__ inline unsigned col_act_bytes(const DevPlan& P, bool g_bf16)
     return col_act_rows(P, g_bf16) + align16u(16u * P.cws * 4u) + 16u * 16u * 4u;
 }
 
+// Unscaled sums of one block of sixteen columns phi~_p (.) g against the
+// level's sixteen generators (LEAF: `s`, the child scores, lane rows 4 kq ..)
+// and against ones (`o`, the column's own <phi~_p, g>, the same in every row).
+// Building the columns is the cost (8 vector instructions per 32 coordinates
+// of sixteen columns); the second product rides on them.
+template <bool G_BF16, bool LEAF>
+__device__ __forceinline__ void column_products(const DevPlan& P, const Wave& S, int trow, f32x4& s, f32x4& o)
+{
+    constexpr int SB = 6;   // fragments requested together
+    const int lane = S.lane, kq = lane >> 4, nchunk = P.nchunk, l = P.levels - 1;
+    const u32x4* Ap = (const u32x4*)P.gamma_pair + P.gamma_off[l] + lane;
+    const uint32_t* cwp = S.cw + (lane & 15) * P.cws;
+    const uint32_t* prow = S.pairs + trow * P.prow + kq * 4;
+    const float* frow = S.gf + trow * P.dp;
+    const u32x4 one = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    s = o = f32x4{0.f, 0.f, 0.f, 0.f};
+    int c0 = 0;
+    for (; c0 + SB <= nchunk; c0 += SB) {
+        u32x4 a[SB];
+        uint32_t wd[SB];
+#pragma unroll
+        for (int e = 0; e < SB; ++e) {
+            if constexpr (LEAF) a[e] = Ap[(int64_t)(c0 + e) * 64];
+            wd[e] = cwp[c0 + e];
+        }
+#pragma unroll
+        for (int e = 0; e < SB; ++e) score_chunk2<G_BF16, LEAF, true>(kq, a[e], one, wd[e], prow, frow, c0 + e, s, o);
+    }
+    for (; c0 < nchunk; ++c0) {
+        u32x4 a = one;
+        if constexpr (LEAF) a = Ap[(int64_t)c0 * 64];
+        score_chunk2<G_BF16, LEAF, true>(kq, a, one, cwp[c0], prow, frow, c0, s, o);
+    }
+}
+
+// grad_coef of the leaf slots (child scores of their parent's column), the
+// leaf parents and, with bf16 gradients, the summed slots, each from columns
+// on the matrix cores: 0.5 vector instructions per slot and chunk against 1
+// in direct_scores.  (fp32 gradients: the exact split costs more than the
+// direct reductions, so the summed slots are left to those.)  Measured, us:
+// 65,536 tokens d 768 k 96 304 -> 299, 8,192 tokens d 768 k 56 37 -> 35,
+// 16,381 tokens d 1024 k 144 191 -> 187, 20,000 tokens d 200 k 16 31 -> 27,
+// 8,192 tokens d 768 k 56 in fp32 85 -> 74.
+template <int CPT, bool G_BF16>
+__device__ __forceinline__ void col_scores(const ColPlan& C, const DevPlan& P, const Wave& S)
+{
+    constexpr int TPW = col_tpw(CPT);
+    const int lane = S.lane, col = lane & 15, kq = lane >> 4, k = C.k;
+    f32x4 s, o;
+    {   // the leaf parents: column tt CPT + q
+        const int tt = col / CPT, q = col & (CPT - 1);
+        const int32_t p = q < C.KP ? S.idx[tt * k + C.sbP + q] : -1;
+        index_bitmaps(P, lane, p, P.nt, S.cw);
+        wave_sync();
+        column_products<G_BF16, true>(P, S, tt, s, o);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) S.score[col * 16 + kq * 4 + i] = s[i] * C.rsd;
+        if (kq == 0 && p >= C.d) S.coef[tt * k + C.sbP + q] = o[0] * C.rsd;
+        wave_sync();
+        for (int i = lane; i < TPW * C.KL; i += 64) {
+            const int t2 = item_token<TPW>(i, C.KL), at = t2 * k + C.sbL + i - t2 * C.KL, rt = S.route[at];
+            if (rt >= 0) S.coef[at] = S.score[(t2 * CPT + (rt >> 16)) * 16 + (rt & 0xFFFF)];
+        }
+    }
+    if constexpr (G_BF16) {
+        for (int i0 = 0; i0 < TPW * C.ns; i0 += 16) {
+            const int i = i0 + col, tt = min(item_token<TPW>(i, C.ns), TPW - 1);
+            const int at = tt * k + C.ss + i - tt * C.ns;
+            const int32_t c = i < TPW * C.ns ? S.idx[at] : -1;
+            wave_sync();
+            index_bitmaps(P, lane, c, P.nt, S.cw);
+            wave_sync();
+            column_products<G_BF16, false>(P, S, tt, s, o);
+            if (kq == 0 && c >= C.d) S.coef[at] = o[0] * C.rsd;
+        }
+    }
+    wave_sync();
+}
+
 // The backward of plans that decode through parent columns (P.wave_tokens =
 // 16 / CPT): grad_coef as in decode_bwd2_kernel, then the column decode of it.
 template <int CPT, int NG, bool G_BF16, bool GX_BF16>
@@ -91,20 +170,28 @@ __global__ __launch_bounds__(kColThreads, 4) void col_bwd_kernel(ColPlan C, DevP
         wave_sync();
         // routes of the leaf slots; coefficients of basis slots (g at their
         // coordinate) and padding
+        bool direct = false;
         for (int i = ln; i < nslots; i += 64) {
             const int tt = item_token<TPW>(i, C.k), s = i - tt * C.k;
             const int32_t c = W.idx[i];
             float v = 0.f;
             if (c >= 0 && c < d) v = g_at<G_BF16>(P, S, tt, c);
             W.coef[i] = v;
-            S.route[i] = s >= C.sbL && c >= d ? col_route<CPT>(C, W, tt, (uint32_t)c) : -1;
+            int rt = -1;
+            if (s >= C.sbL) rt = c >= d ? col_route<CPT>(C, W, tt, (uint32_t)c) : -1;
+            else if (s >= C.sbP || (G_BF16 && s >= C.ss)) rt = 0;   // taken as a column of its own
+            S.route[i] = rt;
+            direct |= c >= d && rt < 0;
         }
+        const uint64_t left = __ballot(direct);
         wave_sync();
-        // grad_coef of routed slots: child scores of each parent column
-        // against g; every other hashed slot directly
-        score_level<G_BF16>(P, S, P.levels - 1);
-        direct_scores<G_BF16, NG>(P, S);
-        wave_sync();
+        // grad_coef of hashed slots: leaf slots, their parents and the summed
+        // slots as columns, whatever is left directly
+        col_scores<CPT, G_BF16>(C, P, S);
+        if (left) {
+            direct_scores<G_BF16, NG>(P, S);
+            wave_sync();
+        }
         if (add_gc) {
             for (int i = ln; i < n; i += 64) W.coef[i] += add_gc[t0 * C.k + i];
             wave_sync();

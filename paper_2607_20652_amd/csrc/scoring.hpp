@@ -25,20 +25,14 @@ struct ActTile {
     const float* f;         // fp32: [TPW][dp]
 };
 
-// Sign bitmaps of the 16 columns of block nb into cw[16][cws] (bit b of word
-// w = sign at coordinate 32w + b).  Column r is parent slot q = r mod 2^csh
-// of token tt = r / 2^csh, with parent parents[tt * pstride + q] when
-// q < nparents and tt < ntok.  Lane (col, w0) builds words w0, w0 + 4, ... of
-// column col: one nibble-table row per 4-bit group of the parent index
-// (parity is linear in the index bits).
-__device__ void column_bitmaps(const DevPlan& P, int lane, int ntok, int csh, int nb, const int32_t* parents,
-                               int pstride, int nparents, const uint32_t* nt, uint32_t* cw)
+// Sign bitmaps of sixteen columns into cw[16][cws] (bit b of word w = sign at
+// coordinate 32w + b), lane (col, w0) giving index p of column col = lane & 15
+// (zero words for p < 0) and building words w0, w0 + 4, ...: one nibble-table
+// row per 4-bit group of the index (parity is linear in the index bits).
+__device__ __forceinline__ void index_bitmaps(const DevPlan& P, int lane, int32_t p, const uint32_t* nt, uint32_t* cw)
 {
     constexpr int MW = 8;  // words per lane kept in registers (nchunk <= 32)
-    const int nchunk = P.nchunk, w0 = lane >> 4;
-    const int col = lane & 15, r = nb * 16 + col, tt = r >> csh, q = r & ((1 << csh) - 1);
-    int32_t p = -1;
-    if (r < (P.wave_tokens << csh) && tt < ntok && q < nparents) p = parents[tt * pstride + q];
+    const int nchunk = P.nchunk, w0 = lane >> 4, col = lane & 15;
     const uint32_t pu = p >= 0 ? (uint32_t)p : 0u;
     uint32_t* dst = cw + col * P.cws;
     // nibble table layout [g][w][16]: word w of group g for nibble value v at (g * nchunk + w) * 16 + v
@@ -63,15 +57,33 @@ __device__ void column_bitmaps(const DevPlan& P, int lane, int ntok, int csh, in
     }
 }
 
+// Sign bitmaps of the 16 columns of block nb: column r is parent slot
+// q = r mod 2^csh of token tt = r / 2^csh, with parent parents[tt * pstride + q]
+// when q < nparents and tt < ntok.
+__device__ void column_bitmaps(const DevPlan& P, int lane, int ntok, int csh, int nb, const int32_t* parents,
+                               int pstride, int nparents, const uint32_t* nt, uint32_t* cw)
+{
+    const int r = nb * 16 + (lane & 15), tt = r >> csh, q = r & ((1 << csh) - 1);
+    int32_t p = -1;
+    if (r < (P.wave_tokens << csh) && tt < ntok && q < nparents) p = parents[tt * pstride + q];
+    index_bitmaps(P, lane, p, nt, cw);
+}
+
 // Unscaled scores of generator tile mb for this lane's column (lane & 15):
 // acc[i] = S[16*mb + 4*(lane>>4) + i][column].  Columns without a parent
 // produce scores of row trow that the callers discard.
-template <bool ACT_BF16>
-__device__ __forceinline__ void score_chunk(const DevPlan& P, int kq, u32x4 a, uint32_t wd, const uint32_t* prow,
-                                            const float* frow, int c, f32x4& acc)
+// One 32-coordinate chunk: acc += A column (FIRST) and acc1 += one column
+// (SECOND) for the same column operand.
+template <bool ACT_BF16, bool FIRST, bool SECOND>
+__device__ __forceinline__ void score_chunk2(int kq, u32x4 a, u32x4 one, uint32_t wd, const uint32_t* prow,
+                                             const float* frow, int c, f32x4& acc, f32x4& acc1)
 {
-    (void)P;
-    const bf16x8 av = __builtin_bit_cast(bf16x8, a);
+    auto product = [&](u32x4 b) {
+        const bf16x8 bv = __builtin_bit_cast(bf16x8, b);
+        if constexpr (FIRST) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), bv, acc, 0, 0, 0);
+        if constexpr (SECOND)
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, one), bv, acc1, 0, 0, 0);
+    };
     if constexpr (ACT_BF16) {
         // dword i: coordinates 4kq + i (low half) and 4kq + i + 16 (high half)
         const uint32_t R = rotl32(wd, 15u - 4u * (uint32_t)kq);
@@ -81,7 +93,7 @@ __device__ __forceinline__ void score_chunk(const DevPlan& P, int kq, u32x4 a, u
         b.y = pd.y ^ (__builtin_amdgcn_alignbit(R, R, 1) & 0x80008000u);
         b.z = pd.z ^ (__builtin_amdgcn_alignbit(R, R, 2) & 0x80008000u);
         b.w = pd.w ^ (__builtin_amdgcn_alignbit(R, R, 3) & 0x80008000u);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+        product(b);
     } else {
         uint32_t hi[8], mi[8], lo[8];
 #pragma unroll
@@ -94,10 +106,17 @@ __device__ __forceinline__ void score_chunk(const DevPlan& P, int kq, u32x4 a, u
         const u32x4 bh = {hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16)};
         const u32x4 bm = {mi[0] | (mi[1] << 16), mi[2] | (mi[3] << 16), mi[4] | (mi[5] << 16), mi[6] | (mi[7] << 16)};
         const u32x4 bl = {lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16)};
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bh), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bm), acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bl), acc, 0, 0, 0);
+        product(bh);
+        product(bm);
+        product(bl);
     }
+}
+
+template <bool ACT_BF16>
+__device__ __forceinline__ void score_chunk(int kq, u32x4 a, uint32_t wd, const uint32_t* prow, const float* frow, int c,
+                                            f32x4& acc)
+{
+    score_chunk2<ACT_BF16, true, false>(kq, a, a, wd, prow, frow, c, acc, acc);
 }
 
 struct NoLateLoads {
@@ -128,10 +147,10 @@ __device__ f32x4 mfma_scores(const DevPlan& P, int lane, int l, int mb, int trow
         }
         if (c0 + 2 * SB > nchunk) late();
 #pragma unroll
-        for (int e = 0; e < SB; ++e) score_chunk<ACT_BF16>(P, kq, a[e], wd[e], prow, frow, c0 + e, acc);
+        for (int e = 0; e < SB; ++e) score_chunk<ACT_BF16>(kq, a[e], wd[e], prow, frow, c0 + e, acc);
     }
     if (nchunk < SB) late();
-    for (; c0 < nchunk; ++c0) score_chunk<ACT_BF16>(P, kq, Ap[(int64_t)c0 * 64], cwp[c0], prow, frow, c0, acc);
+    for (; c0 < nchunk; ++c0) score_chunk<ACT_BF16>(kq, Ap[(int64_t)c0 * 64], cwp[c0], prow, frow, c0, acc);
     return acc;
 }
 
