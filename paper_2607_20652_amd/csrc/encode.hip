@@ -690,6 +690,38 @@ __host__ __device__ inline bool wide_fused(const DevPlan& P, int l)
            wide_gemm_lds(P, l, true) - align16u(kWideCols * 4) >= wide_epi_lds(MT);
 }
 
+// max(m, |a|, |b|); a NaN among them gives NaN.
+__device__ __forceinline__ float max3_abs(float m, float a, float b)
+{
+    return __builtin_elementwise_maximum(m, __builtin_elementwise_maximum(__builtin_fabsf(a), __builtin_fabsf(b)));
+}
+
+// hm shifted left by four, a bit per value: |v| >= tau or unordered.  Two
+// instructions a value (compare, add with carry); each carry is read at
+// least two instructions after its compare, which gfx950 asks for.
+__device__ __forceinline__ uint32_t shift_in_not_less(uint32_t hm, f32x4 v, float tau)
+{
+    uint64_t c0, c1, c2, c3;
+    __asm__("v_cmp_nlt_f32 %1, abs(%5), %9\n\t"
+            "v_cmp_nlt_f32 %2, abs(%6), %9\n\t"
+            "v_cmp_nlt_f32 %3, abs(%7), %9\n\t"
+            "v_cmp_nlt_f32 %4, abs(%8), %9\n\t"
+            "v_addc_co_u32 %0, vcc, %0, %0, %1\n\t"
+            "v_addc_co_u32 %0, vcc, %0, %0, %2\n\t"
+            "v_addc_co_u32 %0, vcc, %0, %0, %3\n\t"
+            "v_addc_co_u32 %0, vcc, %0, %0, %4"
+            : "+v"(hm), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)
+            : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(tau)
+            : "vcc");
+    return hm;
+}
+
+// Set bits of m in lanes below this one.
+__device__ __forceinline__ int lanes_below(uint64_t m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // Scores of tokens [t0 + TT blockIdx.x, ...) of a chunk of ntok tokens at level
 // l into scores[(t - t0) K_{l-1} + q][j] (t0-relative tokens).  MT = 16-row
 // tiles per wave: waves (wr, wc) cover rows 16 MT wr .. and columns 64 wc ..
@@ -862,10 +894,10 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
         if (c + 2 < nchunk) fetch(c + 2, w0);
         if (c + 1 < nchunk) compute(c + 1, w1);
     }
-    // scores (times 1/sqrt d) of the live (token, parent) columns and generator
-    // rows; the fused epilogue takes them (standardized with STD) in place first
+    // scores (times 1/sqrt d; standardized in place already with STD) of the
+    // live (token, parent) columns and generator rows
     const bool all_rows = 32 * MT == D;   // else rows from D on are padding
-    const float osc = FUSE ? 1.f : P.rsd;
+    const float osc = STD ? 1.f : P.rsd;
     auto store_scores = [&](int n) {
         const int col = wc * 64 + n * 16 + c16, tt = col >> csh, q = col & (KC - 1);
         if (tt >= nt_tok || q >= KP) return;
@@ -888,15 +920,9 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
 #pragma unroll
         for (int n = 0; n < 4; ++n) pid[n] = s_pidx[bcol[n]];
         __syncthreads();   // the staging LDS is free from here on
-        // s = acc / sqrt d in place; with standardization z = (s - mu) r, the
+        // with standardization z = (s - mu) r in place (s = acc / sqrt d), the
         // statistics of child p XOR g_row gathered at an index that is always a
         // feature (generator of a clamped row, parent 0 for padding columns)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int n = 0; n < 4; ++n)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[mt][n][i] *= P.rsd;
         if constexpr (STD) {
             const uint32_t* gl = P.gens + P.gens_off[l];
             uint32_t gv[MT][4];
@@ -919,36 +945,59 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
                     for (int mt = 0; mt < MH; ++mt)
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            acc[m0 + mt][n][i] = (acc[m0 + mt][n][i] - st[mt][i].x) * st[mt][i].y;
+                            acc[m0 + mt][n][i] = (acc[m0 + mt][n][i] * P.rsd - st[mt][i].x) * st[mt][i].y;
                 }
             }
         }
+        // The threshold and the hits are taken on |acc|: plain scores are
+        // scaled only where they are written (a multiplication by 1/sqrt d per
+        // value, and a magnitude key of it, were a third of this epilogue).
+        // Padding rows count as 0, whole padding columns as no candidates.
+        if (!all_rows) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool pad = wr * 16 * MT + 16 * mt + 4 * kq + i >= D;
+#pragma unroll
+                    for (int n = 0; n < 4; ++n) acc[mt][n][i] = pad ? 0.f : acc[mt][n][i];
+                }
+        }
         uint32_t* s_top = (uint32_t*)smem;             // [TT][2 row halves][64 lanes]
-        uint32_t* s_tau = s_top + TT * 128;           // [TT]
+        float* s_tau = (float*)(s_top + TT * 128);     // [TT]
         int* s_cnt = (int*)(s_tau + TT);              // [TT]
-        // magnitude key of value i of tile (mt, n): |z| bits + 1, 0 for padding
-        auto mk = [&](int mt, int n, int i) -> uint32_t {
-            const bool ok = (pid[n] >= 0) & (all_rows | (wr * 16 * MT + 16 * mt + 4 * kq + i < D));
-            const uint32_t m = (__float_as_uint(acc[mt][n][i]) & 0x7FFFFFFFu) + 1u;
-            return ok ? m : 0u;
-        };
-        // each lane's largest key per token of this wave
-        for (int u = 0; u < tpw; ++u) {
-            uint32_t top = 0u;
+        // each lane's largest magnitude per column tile, two values an
+        // instruction (a NaN stays one), then per token of this wave
+        uint32_t top[4];
 #pragma unroll
-            for (int n = 0; n < 4; ++n) {
-                if (((n * 16) >> csh) != u) continue;
+        for (int n = 0; n < 4; ++n) {
+            float m = 0.f;
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) top = max(top, mk(mt, n, i));
+            for (int mt = 0; mt < MT; ++mt) {
+                const f32x4 v = acc[mt][n];
+                m = max3_abs(m, v[0], v[1]);
+                m = max3_abs(m, v[2], v[3]);
             }
-            const int tt = ((wc * 64) >> csh) + u;
-            s_top[(tt * 2 + wr) * 64 + lane] = top;
+            top[n] = pid[n] >= 0 ? __float_as_uint(m) & 0x7FFFFFFFu : 0u;
+        }
+        uint32_t* tp = s_top + (((wc * 64) >> csh) * 2 + wr) * 64 + lane;   // 128 words from token to token
+        if (tpw == 4) {
+#pragma unroll
+            for (int n = 0; n < 4; ++n) tp[n * 128] = top[n];
+        } else if (tpw == 2) {
+            tp[0] = max(top[0], top[1]);
+            tp[128] = max(top[2], top[3]);
+        } else {
+            tp[0] = max(max(top[0], top[1]), max(top[2], top[3]));
         }
         if ((int)threadIdx.x < TT) s_cnt[threadIdx.x] = 0;
         __syncthreads();
-        // tau of each token: the K-th largest distinct key among its 128 lane maxima
+        // tau of each token: the K-th largest distinct magnitude among its 128
+        // lane maxima.  Four units in the last place below it are listed too,
+        // so that unequal |acc| that the scaling rounds to one magnitude stay
+        // together (the smaller index wins among them).  Fewer than K distinct
+        // maxima, a NaN, or magnitudes so small that the scaled ones lose
+        // bits list everything.
         for (int tt = wave; tt < TT; tt += 4) {
             uint32_t v[2];
 #pragma unroll
@@ -956,60 +1005,54 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
             sort_desc<2, 6, false>(v, lane, x32);
             uint32_t prev = (uint32_t)__shfl((int)v[1], (lane + 63) & 63, 64);
             if (lane == 0) prev = 0u;
-            int kept = 0, cnt = 0;
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const bool kk = v[r] != 0u && v[r] != prev;
-                kept |= (int)kk << r;
-                cnt += (int)kk;
-                prev = v[r];
-            }
-            int total = 0;
-            int rank = wave_prefix5(cnt, lane, total);
-            uint32_t tau_l = 0u;
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                if (((kept >> r) & 1) && rank == K - 1) tau_l = v[r];
-                rank += (kept >> r) & 1;
-            }
-            const uint64_t hb = __ballot(tau_l != 0u);
-            const uint32_t tau = hb ? (uint32_t)__shfl((int)tau_l, __builtin_ctzll(hb), 64) : 1u;
-            if (lane == 0) s_tau[tt] = tau;
+            const bool k0 = v[0] != 0u && v[0] != prev, k1 = v[1] != 0u && v[1] != v[0];
+            const uint64_t b0 = __ballot(k0), b1 = __ballot(k1);
+            const int rank = lanes_below(b0) + lanes_below(b1);
+            const uint64_t h0 = __ballot(k0 && rank == K - 1), h1 = __ballot(k1 && rank + (int)k0 == K - 1);
+            uint32_t tau = 0u;
+            if (h0) tau = (uint32_t)__builtin_amdgcn_readlane((int)v[0], __builtin_ctzll(h0));
+            else if (h1) tau = (uint32_t)__builtin_amdgcn_readlane((int)v[1], __builtin_ctzll(h1));
+            const uint32_t most = (uint32_t)__builtin_amdgcn_readfirstlane((int)v[0]);
+            constexpr uint32_t kSmall = 0x0D800000u;   // 2^-100
+            tau = (most > 0x7F800000u || tau < kSmall) ? 0u : tau - 4u;
+            if (lane == 0) s_tau[tt] = __uint_as_float(tau);
         }
         __syncthreads();
-        // list the candidates at or above tau in the token's region: each
-        // lane counts its hits of a column tile, a wave prefix gives its
-        // offsets, one LDS atomic per wave and tile reserves the space; the
-        // tile's z values go through the wave's LDS rows so that each lane
-        // visits only its hits
+        // list the candidates at or above tau in the token's region: a bit
+        // per value says which are listed (two instructions each), one LDS
+        // atomic per lane with hits reserves their places (the order of the
+        // list is of no account), and a tile's values go through the wave's LDS
+        // rows so that each lane visits only its hits
         float* zrow = (float*)(smem + kWideEpiZ) + (wave * 64 + lane) * (4 * MT + 4);
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
             const int tt = bcol[n] >> csh, q = bcol[n] & (KC - 1);
-            const uint32_t tau = s_tau[tt];
+            const float tau = s_tau[tt];
             uint64_t* lst = (uint64_t*)(scores + (tb + tt) * KP * D);
-            uint32_t hm = 0u;   // bit 4 mt + i: value (mt, i) is listed
+            uint32_t hm = 0u;   // bit 4 MT - 1 - (4 mt + i): value (mt, i) is listed
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
+            for (int mt = 0; mt < MT; ++mt) hm = shift_in_not_less(hm, acc[mt][n], tau);
+            if (!all_rows) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) hm |= (uint32_t)(mk(mt, n, i) >= tau) << (4 * mt + i);
-            int total = 0;
-            int pos = wave_prefix<6>(__popc(hm), lane, total);   // at most 4 MT = 32 hits
-            int base = 0;
-            if (lane == 0 && total > 0) base = atomicAdd(&s_cnt[tt], total);
-            pos += __shfl(base, 0, 64);
-            if (total == 0) continue;
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (wr * 16 * MT + 16 * mt + 4 * kq + i >= D) hm &= ~(1u << (4 * MT - 1 - (4 * mt + i)));
+            }
+            if (pid[n] < 0) hm = 0u;
+            if (!__ballot(hm != 0u)) continue;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
                 const f32x4 v = acc[mt][n];
                 *(float4*)(zrow + 4 * mt) = make_float4(v[0], v[1], v[2], v[3]);
             }
+            int pos = hm ? atomicAdd(&s_cnt[tt], (int)__popc(hm)) : 0;
             const uint32_t f0 = (uint32_t)(q * D + wr * 16 * MT + 4 * kq);
             while (hm) {
-                const int b = __builtin_ctz(hm);
-                hm &= hm - 1;
+                const int b = 4 * MT - 1 - (31 - __builtin_clz(hm));
+                hm &= ~(0x80000000u >> __builtin_clz(hm));
                 const uint32_t f = f0 + 16u * (uint32_t)(b >> 2) + (uint32_t)(b & 3);
-                if (pos < kWideList) lst[pos] = ((uint64_t)f << 32) | __float_as_uint(zrow[b]);
+                if (pos < kWideList) lst[pos] = ((uint64_t)f << 32) | __float_as_uint(zrow[b] * osc);
                 ++pos;
             }
         }
