@@ -811,16 +811,12 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
     // (two register sets, used in turn)
     struct Words {
         uint32_t a[MT], b[4];
-        u32x4 pd[4];
     };
     auto fetch = [&](int c, Words& W) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) W.a[mt] = s_gb[(rowbase + 16 * mt) * P.cws + c];
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            W.b[n] = cw[bcol[n] * P.cws + c];
-            if constexpr (X_BF16) W.pd[n] = *(const u32x4*)(pairs + btok[n] * P.prow + c * 16 + kq * 4);
-        }
+        for (int n = 0; n < 4; ++n) W.b[n] = cw[bcol[n] * P.cws + c];
     };
     // A dword i: bf16 +-1 pair with the signs at coordinates 4kq + i and 16 + 4kq + i of the chunk
     auto afrag = [&](uint32_t w) -> bf16x8 {
@@ -833,66 +829,133 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
         return __builtin_bit_cast(bf16x8, a);
     };
     auto compute = [&](int c, const Words& W) {
-        if constexpr (X_BF16) {
-            u32x4 b[4];
+        // fp32 activations: each value split exactly into three bf16 terms
+        u32x4 bh[4], bm[4], bl[4];
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            const int tt = btok[n];
+            const uint32_t wd = W.b[n];
+            uint32_t hi[8], mi[8], lo[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+                const int off = 4 * kq + (x >> 1) + 16 * (x & 1);
+                float v = xf[tt * dp + 32 * c + off];
+                v = __uint_as_float(__float_as_uint(v) ^ (((wd >> off) & 1u) << 31));
+                split3(v, hi[x], mi[x], lo[x]);
+            }
+            bh[n] = u32x4{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16)};
+            bm[n] = u32x4{mi[0] | (mi[1] << 16), mi[2] | (mi[3] << 16), mi[4] | (mi[5] << 16), mi[6] | (mi[7] << 16)};
+            bl[n] = u32x4{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16)};
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const bf16x8 av = afrag(W.a[mt]);
 #pragma unroll
             for (int n = 0; n < 4; ++n) {
-                const uint32_t R = rotl32(W.b[n], 15u - 4u * (uint32_t)kq);
-                const u32x4 pd = W.pd[n];
-                b[n].x = pd.x ^ (R & 0x80008000u);
-                b[n].y = pd.y ^ (__builtin_amdgcn_alignbit(R, R, 1) & 0x80008000u);
-                b[n].z = pd.z ^ (__builtin_amdgcn_alignbit(R, R, 2) & 0x80008000u);
-                b[n].w = pd.w ^ (__builtin_amdgcn_alignbit(R, R, 3) & 0x80008000u);
-            }
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const bf16x8 av = afrag(W.a[mt]);
-#pragma unroll
-                for (int n = 0; n < 4; ++n)
-                    acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, b[n]), acc[mt][n],
-                                                                         0, 0, 0);
-            }
-        } else {
-            // fp32 activations: each value split exactly into three bf16 terms
-            u32x4 bh[4], bm[4], bl[4];
-#pragma unroll
-            for (int n = 0; n < 4; ++n) {
-                const int tt = btok[n];
-                const uint32_t wd = W.b[n];
-                uint32_t hi[8], mi[8], lo[8];
-#pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    const int off = 4 * kq + (x >> 1) + 16 * (x & 1);
-                    float v = xf[tt * dp + 32 * c + off];
-                    v = __uint_as_float(__float_as_uint(v) ^ (((wd >> off) & 1u) << 31));
-                    split3(v, hi[x], mi[x], lo[x]);
-                }
-                bh[n] = u32x4{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16)};
-                bm[n] = u32x4{mi[0] | (mi[1] << 16), mi[2] | (mi[3] << 16), mi[4] | (mi[5] << 16), mi[6] | (mi[7] << 16)};
-                bl[n] = u32x4{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16)};
-            }
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const bf16x8 av = afrag(W.a[mt]);
-#pragma unroll
-                for (int n = 0; n < 4; ++n) {
-                    acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bh[n]),
-                                                                         acc[mt][n], 0, 0, 0);
-                    acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bm[n]),
-                                                                         acc[mt][n], 0, 0, 0);
-                    acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bl[n]),
-                                                                         acc[mt][n], 0, 0, 0);
-                }
+                acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bh[n]),
+                                                                     acc[mt][n], 0, 0, 0);
+                acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bm[n]),
+                                                                     acc[mt][n], 0, 0, 0);
+                acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, __builtin_bit_cast(bf16x8, bl[n]),
+                                                                     acc[mt][n], 0, 0, 0);
             }
         }
     };
-    Words w0, w1;
-    fetch(0, w0);
-    for (int c = 0; c < nchunk; c += 2) {
-        if (c + 1 < nchunk) fetch(c + 1, w1);
-        compute(c, w0);
-        if (c + 2 < nchunk) fetch(c + 2, w0);
-        if (c + 1 < nchunk) compute(c + 1, w1);
+    if constexpr (X_BF16) {
+        // Vector instructions and matrix products of the k-loop are balanced
+        // (96 of 4 cycles against 32 of 16 per chunk at MT = 8), so they have
+        // to overlap within a wave: behind every product (mt, n) of chunk c
+        // stand two of the eight instructions that build the next row operand
+        // and its share of those that build the column operands of chunk
+        // c + 1, and the LDS words of chunk c + 2 are requested as the words
+        // they replace are used up.  The order is pinned: left alone, the
+        // compiler builds each operand in one piece between products.
+        constexpr int NS = 4 * MT, BPS = 32 / NS;   // slots per chunk, column instructions per slot
+        u32x4 pd[4], bf[2][4], av[2];
+        uint32_t bw[4], aw[2][MT], RB, RA, tb, ta;
+        const int rot = 15 - 4 * kq;
+        auto fetch_col = [&](int c, int n) {
+            bw[n] = cw[bcol[n] * P.cws + c];
+            pd[n] = *(const u32x4*)(pairs + btok[n] * P.prow + c * 16 + kq * 4);
+        };
+        auto fetch_row = [&](int c, int mt, uint32_t (&a)[MT]) { a[mt] = s_gb[(rowbase + 16 * mt) * P.cws + c]; };
+        // instruction k of the eight that build a column operand (of sign word
+        // w and pairs p), and two (k = 0..3) of the eight of a row operand
+        auto col_op = [&](int k, uint32_t w, const u32x4& p, u32x4& o) {
+            switch (k) {
+            case 0: RB = rotl32(w, (uint32_t)rot); break;
+            case 1: o.x = p.x ^ (RB & 0x80008000u); break;
+            case 2: tb = __builtin_amdgcn_alignbit(RB, RB, 1); break;
+            case 3: o.y = p.y ^ (tb & 0x80008000u); break;
+            case 4: tb = __builtin_amdgcn_alignbit(RB, RB, 2); break;
+            case 5: o.z = p.z ^ (tb & 0x80008000u); break;
+            case 6: tb = __builtin_amdgcn_alignbit(RB, RB, 3); break;
+            default: o.w = p.w ^ (tb & 0x80008000u); break;
+            }
+        };
+        auto row_op = [&](int k, uint32_t w, u32x4& o) {
+            if (k == 0) RA = rotl32(w, (uint32_t)rot);
+            ta = k == 0 ? RA : __builtin_amdgcn_alignbit(RA, RA, k);
+            const uint32_t u = __builtin_amdgcn_bitop3_b32(ta, 0x80008000u, 0x3F803F80u, 0xEA);   // (R & M) | one
+            if (k == 0) o.x = u;
+            else if (k == 1) o.y = u;
+            else if (k == 2) o.z = u;
+            else o.w = u;
+        };
+        // one chunk: cur = its column operands, a = its row words, an = those
+        // of the next chunk (its first row operand is built here)
+        auto chunk = [&](int c, u32x4 (&cur)[4], u32x4 (&next)[4], uint32_t (&a)[MT], uint32_t (&an)[MT]) {
+            const int cf = min(c + 2, nchunk - 1);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+                for (int n = 0; n < 4; ++n) {
+                    const int s = 4 * mt + n;
+                    acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        __builtin_bit_cast(bf16x8, av[mt & 1]), __builtin_bit_cast(bf16x8, cur[n]), acc[mt][n], 0, 0, 0);
+                    row_op(n, mt + 1 < MT ? a[mt + 1 < MT ? mt + 1 : 0] : an[0], av[(mt + 1) & 1]);
+#pragma unroll
+                    for (int u = 0; u < BPS; ++u) {
+                        const int k = s * BPS + u;
+                        col_op(k & 7, bw[k >> 3], pd[k >> 3], next[k >> 3]);
+                        if ((k & 7) == 7) fetch_col(cf, k >> 3);
+                    }
+                    if (n == 3) fetch_row(cf, mt, a);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if constexpr (MT & 1) av[0] = av[1];
+        };
+#pragma unroll
+        for (int n = 0; n < 4; ++n) fetch_col(0, n);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            fetch_row(0, mt, aw[0]);
+            fetch_row(min(1, nchunk - 1), mt, aw[1]);
+        }
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) col_op(k, bw[n], pd[n], bf[0][n]);
+            fetch_col(min(1, nchunk - 1), n);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) row_op(k, aw[0][0], av[0]);
+        int c = 0;
+        for (; c + 1 < nchunk; c += 2) {
+            chunk(c, bf[0], bf[1], aw[0], aw[1]);
+            chunk(c + 1, bf[1], bf[0], aw[1], aw[0]);
+        }
+        if (c < nchunk) chunk(c, bf[0], bf[1], aw[0], aw[1]);
+    } else {
+        Words w0, w1;
+        fetch(0, w0);
+        for (int c = 0; c < nchunk; c += 2) {
+            if (c + 1 < nchunk) fetch(c + 1, w1);
+            compute(c, w0);
+            if (c + 2 < nchunk) fetch(c + 2, w0);
+            if (c + 1 < nchunk) compute(c + 1, w1);
+        }
     }
     // scores (times 1/sqrt d; standardized in place already with STD) of the
     // live (token, parent) columns and generator rows
