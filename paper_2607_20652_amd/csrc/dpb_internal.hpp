@@ -245,6 +245,7 @@ struct dpb_plan {
     dpb::Hierarchy h;
     std::vector<uint32_t> masks_h;   // [d]
     std::vector<uint32_t> gens_h;    // sum Delta_l
+    std::vector<uint32_t> gens_dev;  // the same, in the device's order within each level
     dpb::DevPlan dev{};
     void* dev_alloc = nullptr;       // one device allocation holding every table
 };

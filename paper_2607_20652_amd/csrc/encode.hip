@@ -993,23 +993,23 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) gv[mt][i] = gl[min(wr * 16 * MT + 16 * mt + 4 * kq + i, D - 1)];
-            constexpr int MH = MT > 1 ? MT / 2 : 1;   // row tiles per batch of gathers
+            // a batch is one row tile against the four column tiles: its
+            // generators are neighbours in value
+            uint32_t pu[4];
 #pragma unroll
-            for (int n = 0; n < 4; ++n) {
-                const uint32_t pu = pid[n] >= 0 ? (uint32_t)pid[n] : 0u;
+            for (int n = 0; n < 4; ++n) pu[n] = pid[n] >= 0 ? (uint32_t)pid[n] : 0u;
 #pragma unroll
-                for (int m0 = 0; m0 < MT; m0 += MH) {
-                    float2 st[MH][4];
+            for (int mt = 0; mt < MT; ++mt) {
+                float2 st[4][4];
 #pragma unroll
-                    for (int mt = 0; mt < MH; ++mt)
+                for (int n = 0; n < 4; ++n)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) st[mt][i] = stats[pu ^ gv[m0 + mt][i]];
+                    for (int i = 0; i < 4; ++i) st[n][i] = stats[pu[n] ^ gv[mt][i]];
 #pragma unroll
-                    for (int mt = 0; mt < MH; ++mt)
+                for (int n = 0; n < 4; ++n)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            acc[m0 + mt][n][i] = (acc[m0 + mt][n][i] * P.rsd - st[mt][i].x) * st[mt][i].y;
-                }
+                    for (int i = 0; i < 4; ++i)
+                        acc[mt][n][i] = (acc[mt][n][i] * P.rsd - st[n][i].x) * st[n][i].y;
             }
         }
         // The threshold and the hits are taken on |acc|: plain scores are
