@@ -25,17 +25,61 @@ struct ActTile {
     const float* f;         // fp32: [TPW][dp]
 };
 
+// Words w0 + 4 m, m < MW, of the sign bitmap of index pu, two nibble groups at
+// a time: the XOR of one table row per group (parity is linear in the index
+// bits; table layout [g][w][16]: word w of group g for nibble value v at
+// (g * nchunk + w) * 16 + v).  Every read has a fixed offset from its group's
+// address and each pair of groups folds in one instruction a word.
+template <int MW>
+__device__ __forceinline__ void bitmap_words(const uint32_t* nt, int nchunk, int groups, uint32_t pu, bool live, int w0,
+                                             uint32_t* dst)
+{
+    uint32_t acc[MW];
+#pragma unroll
+    for (int m = 0; m < MW; ++m) acc[m] = 0;
+    const uint32_t* row = nt + w0 * 16;
+    int g = 0;
+    for (; g + 1 < groups; g += 2) {
+        const uint32_t* r0 = row + (pu & 15u);
+        const uint32_t* r1 = row + nchunk * 16 + ((pu >> 4) & 15u);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) acc[m] = __builtin_amdgcn_bitop3_b32(acc[m], r0[64 * m], r1[64 * m], 0x96);
+        row += 2 * nchunk * 16;
+        pu >>= 8;
+    }
+    if (g < groups) {
+        const uint32_t* r0 = row + (pu & 15u);
+#pragma unroll
+        for (int m = 0; m < MW; ++m) acc[m] ^= r0[64 * m];
+    }
+#pragma unroll
+    for (int m = 0; m < MW; ++m) dst[4 * m] = live ? acc[m] : 0u;
+}
+
 // Sign bitmaps of sixteen columns into cw[16][cws] (bit b of word w = sign at
 // coordinate 32w + b), lane (col, w0) giving index p of column col = lane & 15
-// (zero words for p < 0) and building words w0, w0 + 4, ...: one nibble-table
-// row per 4-bit group of the index (parity is linear in the index bits).
+// (zero words for p < 0) and building words w0, w0 + 4, ....  Rows of whole
+// quadruples of up to 32 words take bitmap_words (the parents' bitmaps were
+// 130 of the encoder's 3,866 vector instructions per level and group, 18 for
+// each nibble group); the rest read clamped words.
 __device__ __forceinline__ void index_bitmaps(const DevPlan& P, int lane, int32_t p, const uint32_t* nt, uint32_t* cw)
 {
-    constexpr int MW = 8;  // words per lane kept in registers (nchunk <= 32)
     const int nchunk = P.nchunk, w0 = lane >> 4, col = lane & 15;
     const uint32_t pu = p >= 0 ? (uint32_t)p : 0u;
     uint32_t* dst = cw + col * P.cws;
-    // nibble table layout [g][w][16]: word w of group g for nibble value v at (g * nchunk + w) * 16 + v
+    if ((nchunk & 3) == 0 && nchunk <= 32) {
+        switch (nchunk >> 2) {
+        case 1: return bitmap_words<1>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
+        case 2: return bitmap_words<2>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
+        case 3: return bitmap_words<3>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
+        case 4: return bitmap_words<4>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
+        case 5: return bitmap_words<5>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
+        case 6: return bitmap_words<6>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
+        case 7: return bitmap_words<7>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
+        default: return bitmap_words<8>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
+        }
+    }
+    constexpr int MW = 4;
     for (int wb = 0; wb < nchunk; wb += 4 * MW) {
         uint32_t acc[MW];
         int woff[MW];   // words past nchunk read the last word (in bounds) and are not stored
