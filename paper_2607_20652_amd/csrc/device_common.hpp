@@ -49,12 +49,33 @@ __device__ __forceinline__ float signed_by_parity(float a, uint32_t m)
 }
 
 // AbsTopK key: |s| (fp32 bits) first, then the smaller index; the sign of s
-// rides in bit 0 so that the signed coefficient can be rebuilt.
+// rides in bit 0 so that the signed coefficient can be rebuilt.  A NaN's
+// payload is bounded so that a key's bits, read as a double, are never
+// infinite or NaN: key_max and key_min compare keys as positive doubles.
 __device__ __forceinline__ uint64_t make_key(float s, uint32_t idx)
 {
     const uint32_t u = __float_as_uint(s);
-    return ((uint64_t)(u & 0x7FFFFFFFu) << 32) | (uint64_t)(((0x7FFFFFFFu - idx) << 1) | (u >> 31));
+    return ((uint64_t)min(u & 0x7FFFFFFFu, 0x7FEFFFFFu) << 32) | (uint64_t)(((0x7FFFFFFFu - idx) << 1) | (u >> 31));
 }
+
+// Larger and smaller of two keys, one instruction each: positive finite
+// doubles order as their bits do, denormals included (the fp64 denormal mode
+// is on), and v_max_f64 runs at the full vector rate here (a 64-bit compare and
+// two selects take three).
+__device__ __forceinline__ uint64_t key_max(uint64_t a, uint64_t b)
+{
+    uint64_t r;
+    __asm__("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ uint64_t key_min(uint64_t a, uint64_t b)
+{
+    uint64_t r;
+    __asm__("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ uint32_t key_max(uint32_t a, uint32_t b) { return max(a, b); }
+__device__ __forceinline__ uint32_t key_min(uint32_t a, uint32_t b) { return min(a, b); }
 __device__ __forceinline__ uint32_t key_index(uint64_t key) { return 0x7FFFFFFFu - ((uint32_t)key >> 1); }
 __device__ __forceinline__ float key_value(uint64_t key)
 {

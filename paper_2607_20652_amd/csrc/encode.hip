@@ -61,8 +61,10 @@ __host__ __device__ inline EncLayout enc_layout(const DevPlan& P, bool act_bf16,
     // level-0 candidates: the K_0 lanes whose maximum reaches tau, each with all
     // its keys; listn counts 64-bit words per token.  Plain bf16 keys are 32
     // bits (2 ND per lane, two to a word); standardized and fp32 keys are 64.
-    const int listn = (act_bf16 && !std) ? P.active[0] * ND
-                                         : P.active[0] * (act_bf16 ? 2 * ND : (P.d + LPT - 1) / LPT);
+    // The beam levels' selection keeps two keys per lane of a token there.
+    const int level0 = (act_bf16 && !std) ? P.active[0] * ND
+                                          : P.active[0] * (act_bf16 ? 2 * ND : (P.d + LPT - 1) / LPT);
+    const int listn = level0 > 2 * LPT ? level0 : 2 * LPT;
     L.listn = listn;
     L.kmaxp = P.kmax;
     unsigned off = 0;
@@ -83,33 +85,6 @@ __host__ __device__ inline unsigned enc_shared_bytes(const DevPlan& P, bool std)
     return align16u(P.nt_groups * 16 * P.nchunk * 4) + align16u(P.gens_total * 4) + (std ? align16u(P.d * 8) : 0u);
 }
 
-// Exchange with the lane whose index differs by m (a power of two): DPP for
-// 1 and 2, swizzles up to 16, a permute for 32 (the LDS-path exchanges cost
-// no vector-ALU slots, which the encoder is short of).
-__device__ __forceinline__ uint32_t xlane(uint32_t v, int m, int x32addr)
-{
-    switch (m) {
-    case 1: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);
-    case 2: return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);
-    case 4: return swz_xor<4>(v);
-    case 8: return swz_xor<8>(v);
-    case 16: return swz_xor<16>(v);
-    default: return (uint32_t)__builtin_amdgcn_ds_bpermute(x32addr, (int)v);
-    }
-}
-
-__device__ __forceinline__ uint64_t xlane64(uint64_t v, int m, int x32addr)
-{
-    return ((uint64_t)xlane((uint32_t)(v >> 32), m, x32addr) << 32) | xlane((uint32_t)v, m, x32addr);
-}
-
-template <typename K>
-__device__ __forceinline__ K xlaneK(K v, int m, int x32addr)
-{
-    if constexpr (sizeof(K) == 8) return xlane64(v, m, x32addr);
-    else return xlane(v, m, x32addr);
-}
-
 __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src)
 {
     const uint32_t hi = (uint32_t)__shfl((int)(v >> 32), src, 64);
@@ -117,45 +92,98 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src)
     return ((uint64_t)hi << 32) | lo;
 }
 
+// The value of the lane whose index differs by the bits of M.
+template <int M, typename K>
+__device__ __forceinline__ K xlane_mask(K v, int x32addr)
+{
+    auto one = [&](uint32_t w) -> uint32_t {
+        if constexpr (M == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xF, 0xF, false);
+        else if constexpr (M == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0x4E, 0xF, 0xF, false);
+        else if constexpr (M < 32) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)w, (M << 10) | 0x1F);
+        else return (uint32_t)__builtin_amdgcn_ds_bpermute(x32addr ^ ((M ^ 32) << 2), (int)w);
+    };
+    if constexpr (sizeof(K) == 8) return ((uint64_t)one((uint32_t)(v >> 32)) << 32) | one((uint32_t)v);
+    else return one(v);
+}
+
+// Lane bits of position bit B, and of position bits 0 .. B (see sort_desc).
+template <bool MFMA_LAYOUT, int B>
+constexpr int lane_bit() { return MFMA_LAYOUT ? (B < 2 ? (16 << B) : (1 << (B - 2))) : (1 << B); }
+template <bool MFMA_LAYOUT, int B>
+constexpr int lane_bits()
+{
+    if constexpr (B < 0) return 0;
+    else return lane_bit<MFMA_LAYOUT, B>() | lane_bits<MFMA_LAYOUT, B - 1>();
+}
+
+// One exchange with the lanes at mask M: the lane with position bit B clear
+// keeps the larger keys.  FLIP: against the other lane's registers in reverse.
+template <int R, int M, int B, bool FLIP, typename K>
+__device__ __forceinline__ void sort_lanes(K (&v)[R], int lanepos, int x32addr)
+{
+    const bool lower = !((lanepos >> B) & 1);
+    K o[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) o[r] = xlane_mask<M>(v[FLIP ? R - 1 - r : r], x32addr);
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = ((o[r] > v[r]) == lower) ? o[r] : v[r];
+}
+
+template <int R, bool MFMA_LAYOUT, int JS, typename K>
+__device__ __forceinline__ void sort_halves(K (&v)[R], int lanepos, int x32addr)
+{
+    constexpr int LR = R == 1 ? 0 : R == 2 ? 1 : R == 4 ? 2 : R == 8 ? 3 : 4;
+    if constexpr (JS >= 0) {
+        if constexpr (JS >= LR) {
+            sort_lanes<R, lane_bit<MFMA_LAYOUT, JS - LR>(), JS - LR, false>(v, lanepos, x32addr);
+        } else {
+            constexpr int j = 1 << JS;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (r & j) continue;
+                const K a = v[r], c = v[r | j];
+                v[r] = key_max(a, c);
+                v[r | j] = key_min(a, c);
+            }
+        }
+        sort_halves<R, MFMA_LAYOUT, JS - 1>(v, lanepos, x32addr);
+    }
+}
+
+template <int R, int NB, bool MFMA_LAYOUT, int KS, typename K>
+__device__ __forceinline__ void sort_merge(K (&v)[R], int lanepos, int x32addr)
+{
+    constexpr int LR = R == 1 ? 0 : R == 2 ? 1 : R == 4 ? 2 : R == 8 ? 3 : 4;
+    if constexpr (KS <= LR + NB) {
+        if constexpr (KS > LR) {
+            sort_lanes<R, lane_bits<MFMA_LAYOUT, KS - LR - 1>(), KS - LR - 1, true>(v, lanepos, x32addr);
+        } else {
+            constexpr int mirror = (1 << KS) - 1;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if ((r ^ mirror) < r) continue;
+                const K a = v[r], c = v[r ^ mirror];
+                v[r] = key_max(a, c);
+                v[r ^ mirror] = key_min(a, c);
+            }
+        }
+        sort_halves<R, MFMA_LAYOUT, KS - 2>(v, lanepos, x32addr);
+        sort_merge<R, NB, MFMA_LAYOUT, KS + 1>(v, lanepos, x32addr);
+    }
+}
+
 // Descending bitonic sort of one token's R * 2^NB keys: element e =
 // lanepos * R + r lives in register r of the lane at position lanepos.  In
 // the MFMA layout lanepos = q * 4 + kq (q = lane bits 0.., kq = lane bits
-// 4, 5); otherwise lanepos bit b is lane bit b.  Every loop is unrolled, so
-// the exchange pattern and the in-lane directions are compile-time constants.
+// 4, 5); otherwise lanepos bit b is lane bit b.  Each merge first compares an
+// element with its mirror image in the block, so every block is sorted
+// descending and no comparison's direction depends on the lane: a
+// compare-exchange within a lane is one maximum and one minimum (the form with
+// alternating directions took five instructions for 64-bit keys).
 template <int R, int NB, bool MFMA_LAYOUT, typename K>
 __device__ __forceinline__ void sort_desc(K (&v)[R], int lanepos, int x32addr)
 {
-    constexpr int LR = R == 1 ? 0 : R == 2 ? 1 : R == 4 ? 2 : R == 8 ? 3 : 4;
-#pragma unroll
-    for (int ks = 1; ks <= LR + NB; ++ks) {
-#pragma unroll
-        for (int js = ks - 1; js >= 0; --js) {
-            if (js >= LR) {
-                const int b = js - LR;
-                const int m = MFMA_LAYOUT ? (b < 2 ? (16 << b) : (1 << (b - 2))) : (1 << b);
-                const bool up = (ks - LR < NB) && ((lanepos >> (ks - LR)) & 1);
-                const bool lower = !((lanepos >> b) & 1);
-                const bool tmax = lower != up;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const K o = xlaneK(v[r], m, x32addr);
-                    const bool gt = o > v[r];
-                    v[r] = (gt == tmax) ? o : v[r];
-                }
-            } else {
-                const int j = 1 << js;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    if (r & j) continue;
-                    const bool up = (ks < LR) ? ((r >> ks) & 1) : ((ks - LR < NB) && ((lanepos >> (ks - LR)) & 1));
-                    const K a = v[r], c = v[r | j];
-                    const bool sw = up ? (a > c) : (a < c);
-                    v[r] = sw ? c : a;
-                    v[r | j] = sw ? a : c;
-                }
-            }
-        }
-    }
+    sort_merge<R, NB, MFMA_LAYOUT, 1>(v, lanepos, x32addr);
 }
 
 // Emits the first K distinct keys of each token straight from the sorted
@@ -512,60 +540,85 @@ __global__ __launch_bounds__(kEncThreads, (X_BF16 && (CPT == 16 || CPT == 8) && 
                 }
             }
             // Levels that keep few of their candidates (K_l <= 2 CPT, the beam
-            // levels): the K_l-th largest distinct lane maximum tau bounds the
-            // answer (at least K_l distinct keys reach it), only the keys >= tau
-            // are listed, and that short list (one key per lane of the token) is
-            // sorted and emitted.  A token with more keys >= tau than lanes, or
-            // any other level, sorts all its keys.
+            // levels): the K_l-th largest lane maximum tau bounds the answer (at
+            // least K_l keys reach it); the keys with a magnitude >= tau are
+            // listed (at most one per lane of the token), each lane counts
+            // the listed keys above its own, and the key goes to that place of
+            // a second list.  Equal keys (a child reached from two parents)
+            // share a place and leave the next one empty, so the distinct keys
+            // are the occupied places in order.  A token with more listed keys
+            // than lanes, or with fewer than K_l distinct ones although not
+            // all are listed, sorts all its keys.  (Sorting the list as 64-bit
+            // keys and ranking by ballots took 270 vector instructions a
+            // level, this takes about 150; with the sort of fixed directions:
+            // 65,536 tokens d 768 268 -> 238 us, 16,384 tokens d 1024 N 2^24
+            // 188 -> 171, standardized 367 -> 331.)
             const int Kl = P.active[l];
             bool done = false;
-            if (Kl <= 2 * CPT && EL.listn >= 4 * CPT) {
-                // the lane maxima are sorted by their magnitude word alone:
-                // K_l distinct magnitudes at or above tau are K_l distinct
-                // children, so tau = (that magnitude, lowest low word) still
-                // admits the K_l largest keys (a valid key of magnitude 0
-                // counts as none: then tau = 1)
-                uint64_t m64 = keys[0];
+            if (Kl <= 2 * CPT) {
+                uint32_t mg[R], top[1] = {0u};
 #pragma unroll
-                for (int r = 1; r < R; ++r) m64 = keys[r] > m64 ? keys[r] : m64;
-                uint32_t mx[1] = {(uint32_t)(m64 >> 32)};
-                sort_desc<1, NB, true>(mx, lanepos, x32);
-                const uint32_t ph = (uint32_t)__builtin_amdgcn_ds_bpermute(prev_addr, (int)mx[0]);
-                const uint32_t prev = lanepos > 0 ? ph : 0u;
-                const bool kept = mx[0] != 0u && mx[0] != prev;
-                const int rank = (int)__popcll(__ballot(kept) & before_mask);
-                const uint64_t owner = __ballot(kept && rank == Kl - 1) & token_mask;
-                uint64_t tau = 1ull;   // fewer than K_l distinct maxima: every key
-                if (owner) {
-                    const int oa = (int)__builtin_ctzll(owner) << 2;
-                    tau = (uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(oa, (int)mx[0]) << 32;
+                for (int r = 0; r < R; ++r) {
+                    mg[r] = (uint32_t)(keys[r] >> 32);
+                    top[0] = max(top[0], mg[r]);
                 }
-                int c = 0;
+                uint64_t* tl = list + ct * EL.listn;
+                uint64_t* placed = tl + 4 * CPT;
+                tl[lanepos] = 0ull;
+                placed[lanepos] = 0ull;
+                if (lanepos == 0) cnt[ct] = 0;
+                sort_desc<1, NB, true>(top, lanepos, x32);
+                // the lane at position K_l - 1 of my token
+                const int at = Kl - 1, src = ct * CPT + (at >> 2) + 16 * (at & 3);
+                const uint32_t tau = (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)top[0]);
+                uint32_t hits = 0u;
 #pragma unroll
-                for (int r = 0; r < R; ++r) c += (int)(keys[r] >= tau);
-                // c <= R keys per lane (R = 4, 8 or 16): 3, 4 or 5 count bits
-                constexpr int CBITS = R <= 4 ? 3 : R <= 8 ? 4 : 5;
-                int before = 0, total = 0;
+                for (int r = 0; r < R; ++r) hits |= (uint32_t)(keys[r] != 0ull && mg[r] >= tau) << r;
+                wave_sync();
+                int pos = hits ? atomicAdd(&cnt[ct], (int)__popc(hits)) : 0;
 #pragma unroll
-                for (int b = 0; b < CBITS; ++b) {
-                    const uint64_t m = __ballot((c >> b) & 1);
-                    before += (int)__popcll(m & before_mask) << b;
-                    total += (int)__popcll(m & token_mask) << b;
-                }
-                if (!__ballot(total > 4 * CPT)) {
-                    uint64_t* tl = list + ct * EL.listn;
-                    int pos = before;
+                for (int r = 0; r < R; ++r)
+                    if ((hits >> r) & 1u) {
+                        if (pos < 4 * CPT) tl[pos] = keys[r];
+                        ++pos;
+                    }
+                wave_sync();
+                const int n = cnt[ct];
+                if (!__ballot(n > 4 * CPT)) {
+                    const uint64_t e = tl[lanepos];
+                    int above = 0;
+                    for (int f = 0; __ballot(f < n); f += 4) {
 #pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        if (keys[r] >= tau) tl[pos++] = keys[r];
+                        for (int u = 0; u < 4; ++u) above += (int)(tl[f + u] > e);
+                    }
+                    if (e != 0ull) placed[above] = e;
                     wave_sync();
-                    uint64_t one[1] = {lanepos < total ? tl[lanepos] : 0ull};
-                    wave_sync();
-                    sort_desc<1, NB, true>(one, lanepos, x32);
-                    emit_mfma<1, CPT>(P, one, lane, lanepos, ct, prev_addr, before_mask, token_mask, t0, ntok, Kl,
-                                      P.slot_base[l], par, EL.kmaxp, out_idx, out_coef);
-                    done = true;
+                    const uint64_t k = placed[lanepos];
+                    const uint64_t full = __ballot(k != 0ull);
+                    const int rank = (int)__popcll(full & before_mask), total = (int)__popcll(full & token_mask);
+                    if (!__ballot(total < Kl && tau != 0u)) {
+                        int32_t* pr = par + ct * EL.kmaxp;
+                        const bool live = ct < ntok;
+                        const int64_t o = (t0 + ct) * P.k_tot + P.slot_base[l];
+                        if (k != 0ull && rank < Kl) {
+                            const uint32_t ci = key_index(k);
+                            pr[rank] = (int32_t)ci;
+                            if (live) {
+                                out_idx[o + rank] = (int32_t)ci;
+                                out_coef[o + rank] = key_value(k);
+                            }
+                        }
+                        for (int r = total + lanepos; r < Kl; r += 4 * CPT) {
+                            pr[r] = -1;
+                            if (live) {
+                                out_idx[o + r] = -1;
+                                out_coef[o + r] = 0.f;
+                            }
+                        }
+                        done = true;
+                    }
                 }
+                wave_sync();
             }
             if (!done) {
                 sort_desc<R, NB, true>(keys, lanepos, x32);
