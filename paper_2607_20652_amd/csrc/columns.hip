@@ -5,7 +5,7 @@ namespace dpb {
 namespace {
 
 template <int CPT, int NG, bool OUT_BF16>
-__global__ __launch_bounds__(kColThreads, 4) void col_decode_kernel(ColPlan C, const int32_t* __restrict__ idx,
+__global__ __launch_bounds__(kColThreads, col_decode_waves(CPT)) void col_decode_kernel(ColPlan C, const int32_t* __restrict__ idx,
                                                                     const float* __restrict__ coef, int64_t T,
                                                                     void* __restrict__ y)
 {
@@ -73,7 +73,7 @@ static void launch_col_v(const ColPlan& C, size_t lds, hipStream_t stream, const
                          int64_t T, void* y)
 {
     allow_lds(col_decode_kernel<CPT, NG, OB>, lds);
-    hipLaunchKernelGGL((col_decode_kernel<CPT, NG, OB>), col_grid(T, col_tpw(CPT), lds, 4, 1), dim3(kColThreads), lds,
+    hipLaunchKernelGGL((col_decode_kernel<CPT, NG, OB>), col_grid(T, col_tpw(CPT), lds, col_decode_waves(CPT), 1), dim3(kColThreads), lds,
                        stream, C, idx, coef, T, y);
 }
 
@@ -95,12 +95,13 @@ template <bool OB>
 static bool launch_col(const DevPlan& P, const int32_t* idx, const float* coef, int64_t T, void* y, hipStream_t stream)
 {
     const int cpt = col_cpt(P);
-    if (!cpt) return false;
+    if (cpt < 0) return false;
     const ColPlan C = col_plan(P, cpt);
     const size_t lds = col_shared_bytes(C) + (size_t)kColWaves * col_layout(C, cpt, 0).bytes;
     if (lds > (size_t)kLdsBudget) return false;
     const int ng = ng_variant(P);
-    if (cpt == 4) launch_col_ng<4, OB>(ng, C, lds, stream, idx, coef, T, y);
+    if (cpt == 0) launch_col_ng<0, OB>(ng, C, lds, stream, idx, coef, T, y);
+    else if (cpt == 4) launch_col_ng<4, OB>(ng, C, lds, stream, idx, coef, T, y);
     else if (cpt == 8) launch_col_ng<8, OB>(ng, C, lds, stream, idx, coef, T, y);
     else launch_col_ng<16, OB>(ng, C, lds, stream, idx, coef, T, y);
     return true;

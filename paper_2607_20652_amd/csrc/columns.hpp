@@ -69,11 +69,22 @@ struct ColPlan {
 
 constexpr int kColWaves = 4;
 constexpr int kColThreads = 64 * kColWaves;
+// Waves per SIMD the kernels are held to by registers.
+constexpr int col_decode_waves(int cpt) { return cpt ? 4 : 8; }
+constexpr int col_bwd_waves(int cpt) { return cpt ? 4 : 5; }
 constexpr int kColMaxSlots = 254;   // a mark holds slot + 1 in a byte
 
-// Listed indices of word 0: the nibbles that hold no parent bits.
-__host__ __device__ constexpr int col_word0_slots(int cpt) { return cpt == 16 ? 16 : 24; }
-__host__ __device__ constexpr int col_tpw(int cpt) { return 16 / cpt; }
+// CPT = 0: a plan without leaf columns.  One token per wave, every hashed slot
+// is summed through the tables, and the matrix cores take no part in a step.
+// Against the row-in-LDS kernels, us: decode of 16,384 tokens pt_small_3l
+// 93 -> 76, 8,192 tokens pt_large_2l 58 -> 36, 20,000 tokens d 64 k 48
+// 37 -> 15; backward 236 -> 177, 109 -> 82, and 20,000 tokens d 256 k 64
+// 98 -> 52.
+// Nibbles of each half-word of word 0 that hold parent bits, and the listed
+// indices that leaves.
+__host__ __device__ constexpr int col_parent_nibbles(int cpt) { return cpt == 16 ? 2 : cpt ? 1 : 0; }
+__host__ __device__ constexpr int col_word0_slots(int cpt) { return 32 - 8 * col_parent_nibbles(cpt); }
+__host__ __device__ constexpr int col_tpw(int cpt) { return cpt ? 16 / cpt : 1; }
 
 // LDS of a column wave (byte offsets inside its region).  `act` is the first
 // byte of a region of act_bytes that the caller uses before the decode (the
@@ -211,7 +222,8 @@ __device__ __forceinline__ int item_token(int i, int n)
 template <int CPT>
 __device__ __forceinline__ void col_parents(const ColPlan& C, const ColWave& W)
 {
-    if (W.lane < 16) {
+    if constexpr (CPT == 0) return;
+    else if (W.lane < 16) {
         const int tt = W.lane / CPT, q = W.lane & (CPT - 1);
         const int32_t p = q < C.KP ? W.idx[tt * C.k + C.sbP + q] : -1;
         const uint32_t u = p >= 0 ? (uint32_t)p : ~0u;
@@ -227,7 +239,7 @@ template <int CPT>
 __device__ __forceinline__ int col_route(const ColPlan& C, const ColWave& W, int tt, uint32_t c)
 {
     const uint32_t hc = ((c ^ (c >> C.hshift)) & C.hmask) << 3;
-    constexpr int B = CPT < 8 ? CPT : 8;
+    constexpr int B = CPT < 8 ? (CPT ? CPT : 1) : 8;
     int rt = -1;
 #pragma unroll
     for (int q0 = CPT - B; q0 >= 0; q0 -= B) {
@@ -276,7 +288,7 @@ __device__ __forceinline__ ColFrag col_frag(const float* alpha, int lane)
 template <int CPT, int NG>
 __device__ __forceinline__ void col_tables(const ColPlan& C, const ColWave& W, const float* cf)
 {
-    constexpr int TPW = col_tpw(CPT), PN = CPT == 16 ? 2 : 1;
+    constexpr int TPW = col_tpw(CPT), PN = col_parent_nibbles(CPT);
     const int lane = W.lane, b = lane & 31, v = lane & 15;
     const uint32_t x0 = -(uint32_t)(v & 1), x1 = -(uint32_t)((v >> 1) & 1), x2 = -(uint32_t)((v >> 2) & 1),
                    x3 = -(uint32_t)((v >> 3) & 1);
@@ -386,19 +398,20 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
                                           f32x4 c0, int nx, int64_t row0, void* out, const void* add)
 {
     constexpr int TPW = col_tpw(CPT), LPT = 64 / TPW, NP = LPT / 16;   // NP 16-column blocks per pair half
-    constexpr int PN = CPT == 16 ? 2 : 1;
+    constexpr int PN = col_parent_nibbles(CPT);
     const int lane = W.lane, row = lane & 15, kq = lane >> 4, ll = lane & (LPT - 1);
     const int tt = lane / LPT;
     const uint32_t vb = lds_addr(W.tab) + (uint32_t)(tt * C.words) * 1024u, tb = vb + 512u;
     const u32x4* mk = W.mask + ll;
     const unsigned char* mark = W.mark + tt * C.mstride + 2 * ll;
-    const int sh0 = 15 - 2 * (kq & (CPT / 4 - 1));
+    const int sh0 = CPT ? 15 - 2 * (kq & (CPT / 4 - 1)) : 0;
     // B operands: coordinates 2 LPT m + 32 p + 2 row + {0, 1}, generators 4 kq .. (16 bytes hold both).
     // Addresses here and of the rows are a scalar base plus a 32-bit lane offset.
     const char* bfr = (const char*)C.gamma_t;
     const int blocks2 = C.dp / 32;                       // pairs of 16-coordinate blocks
     const uint32_t boff = 16u * (uint32_t)((row >> 3) * 32 + (row & 7) + 8 * kq);   // block, column pair, generators
     auto fetch = [&](int m, u32x4 (&B)[NP]) {
+        if constexpr (CPT == 0) return;
 #pragma unroll
         for (int p = 0; p < NP; ++p)
             B[p] = *(const u32x4*)(bfr + (size_t)(1024u * (uint32_t)min(m * NP + p, blocks2 - 1)) + boff);
@@ -420,7 +433,7 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
         // columns: products of both coordinates of every block
         f32x4 acc[2][NP];
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
+        for (int p = 0; p < (CPT ? NP : 0); ++p) {
             const bf16x4 g0 = __builtin_bit_cast(bf16x4, (u32x2){B[p].x, B[p].y});
             const bf16x4 g1 = __builtin_bit_cast(bf16x4, (u32x2){B[p].z, B[p].w});
             acc[0][p] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(F.hi, g0, c0, 0, 0, 0);
@@ -479,6 +492,10 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
         float y[2];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
+            if constexpr (CPT == 0) {
+                y[e] = t[e];
+                continue;
+            }
             uint32_t Up[NP];
             if constexpr (NP == 1) {
                 Up[0] = U[e];
@@ -581,23 +598,29 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
                                            const void* add)
 {
     const int lane = W.lane;
-    if (lane < 16) {
-        const int tt = lane / CPT, q = lane & (CPT - 1);
-        const uint32_t p = W.par[lane].x;
-        W.pc[lane] = p != ~0u && p >= (uint32_t)C.d ? cf[tt * C.k + C.sbP + q] : 0.f;
+    ColFrag F{};
+    f32x4 c0{};
+    if constexpr (CPT > 0) {
+        if (lane < 16) {
+            const int tt = lane / CPT, q = lane & (CPT - 1);
+            const uint32_t p = W.par[lane].x;
+            W.pc[lane] = p != ~0u && p >= (uint32_t)C.d ? cf[tt * C.k + C.sbP + q] : 0.f;
+        }
+        wave_sync();
+        F = col_frag<!OUT_BF16>((const float*)W.tab, lane);
+        c0 = *(const f32x4*)(W.pc + 4 * (lane >> 4));
+        wave_sync();
     }
-    wave_sync();
-    const ColFrag F = col_frag<!OUT_BF16>((const float*)W.tab, lane);
-    const f32x4 c0 = *(const f32x4*)(W.pc + 4 * (lane >> 4));
-    wave_sync();
     col_tables<CPT, NG>(C, W, cf);
     const int nx = col_marks<CPT>(C, W, cf);
     wave_sync();
     const int g0 = min(C.ns, col_word0_slots(CPT));
+    constexpr int MG = col_word0_slots(CPT) / 4;   // groups of word 0
     if (g0 == 0) col_steps<CPT, NG, OUT_BF16, 0>(C, W, cf, F, c0, nx, row0, out, add);
     else if (g0 <= 8) col_steps<CPT, NG, OUT_BF16, 2>(C, W, cf, F, c0, nx, row0, out, add);
-    else if (CPT == 16 || g0 <= 16) col_steps<CPT, NG, OUT_BF16, 4>(C, W, cf, F, c0, nx, row0, out, add);
-    else col_steps<CPT, NG, OUT_BF16, 6>(C, W, cf, F, c0, nx, row0, out, add);
+    else if (MG == 4 || g0 <= 16) col_steps<CPT, NG, OUT_BF16, 4>(C, W, cf, F, c0, nx, row0, out, add);
+    else if (MG == 6 || g0 <= 24) col_steps<CPT, NG, OUT_BF16, MG < 6 ? 4 : 6>(C, W, cf, F, c0, nx, row0, out, add);
+    else col_steps<CPT, NG, OUT_BF16, MG>(C, W, cf, F, c0, nx, row0, out, add);
     wave_sync();
 }
 
@@ -607,6 +630,7 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
 template <int CPT, typename Route>
 __device__ __forceinline__ void col_alpha(const ColPlan& C, const ColWave& W, const float* cf, Route route)
 {
+    if constexpr (CPT == 0) return;
     constexpr int TPW = col_tpw(CPT);
     float* alpha = (float*)W.tab;
     *(float4*)(alpha + 4 * W.lane) = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -630,13 +654,14 @@ struct CodeFetch {
     float c[kWords];
 };
 
-// Parent columns per token of the column decode (columns.hpp), or 0 when the
-// plan does not decode its last level through them: the old decode then
-// lists every slot in its tables.
+// Parent columns per token of the column decode: the last level's where it
+// decodes through them, else 0 (every hashed slot through the tables); -1 for
+// codes wider than a mark, which the row-in-LDS kernels of codes.hip take.
 inline int col_cpt(const DevPlan& P)
 {
     const int L1 = P.levels - 1;
-    if (!P.leaf_columns || P.gtab_total <= 0 || P.k_tot > kColMaxSlots || P.cpt[L1] < 4 || P.cpt[L1] > 16) return 0;
+    if (P.k_tot > kColMaxSlots) return -1;
+    if (!P.leaf_columns || P.gtab_total <= 0 || P.cpt[L1] < 4 || P.cpt[L1] > 16) return 0;
     return P.cpt[L1];
 }
 
@@ -650,19 +675,23 @@ inline ColPlan col_plan(const DevPlan& P, int cpt)
     C.mstride = 2 * lpt * C.steps;
     C.k = P.k_tot;
     C.K0 = P.active[0];
-    C.KP = P.active[L1 - 1];
-    C.sbP = P.slot_base[L1 - 1];
-    C.KL = P.active[L1];
-    C.sbL = P.slot_base[L1];
     C.ss = P.active[0];
+    C.sbP = C.sbL = P.k_tot;
+    C.gtab = P.gtab;
+    C.masks = P.masks;
+    C.rsd = P.rsd;
+    if (cpt) {
+        C.KP = P.active[L1 - 1];
+        C.sbP = P.slot_base[L1 - 1];
+        C.KL = P.active[L1];
+        C.sbL = P.slot_base[L1];
+        C.hmask = (1u << P.gtab_bits[L1]) - 1u;
+        C.hshift = P.gtab_shift[L1];
+        C.gtab = P.gtab + 2 * (size_t)P.gtab_off[L1];
+        C.gamma_t = (const char*)P.gamma_t + 8 * P.gamma_t_off[L1];
+    }
     C.ns = std::max(0, C.sbP - C.K0);
     C.words = 1 + (std::max(0, C.ns - col_word0_slots(cpt)) + 31) / 32;
-    C.rsd = P.rsd;
-    C.hmask = (1u << P.gtab_bits[L1]) - 1u;
-    C.hshift = P.gtab_shift[L1];
-    C.gtab = P.gtab + 2 * (size_t)P.gtab_off[L1];
-    C.masks = P.masks;
-    C.gamma_t = (const char*)P.gamma_t + 8 * P.gamma_t_off[L1];
     return C;
 }
 

@@ -10,9 +10,16 @@ __host__ __device__ inline unsigned col_act_rows(const DevPlan& P, bool g_bf16)
 {
     return align16u((unsigned)P.wave_tokens * (g_bf16 ? P.prow : P.dp) * 4u);
 }
-__host__ __device__ inline unsigned col_act_bytes(const DevPlan& P, bool g_bf16)
+// The score tile (and the direct reductions' list) of a plan without leaf
+// columns shares the bitmaps' space: it has no scores, and lists after them.
+__host__ __device__ inline unsigned col_act_bitmaps(const DevPlan& P, int cpt)
 {
-    return col_act_rows(P, g_bf16) + align16u(16u * P.cws * 4u) + 16u * 16u * 4u;
+    const unsigned b = align16u(16u * P.cws * 4u);
+    return cpt ? b : b > 1024u ? b : 1024u;
+}
+__host__ __device__ inline unsigned col_act_bytes(const DevPlan& P, int cpt, bool g_bf16)
+{
+    return col_act_rows(P, g_bf16) + col_act_bitmaps(P, cpt) + (cpt ? 1024u : 0u);
 }
 
 // Unscaled sums of one block of sixteen columns phi~_p (.) g against the
@@ -64,7 +71,7 @@ __device__ __forceinline__ void col_scores(const ColPlan& C, const DevPlan& P, c
     constexpr int TPW = col_tpw(CPT);
     const int lane = S.lane, col = lane & 15, kq = lane >> 4, k = C.k;
     f32x4 s, o;
-    {   // the leaf parents: column tt CPT + q
+    if constexpr (CPT > 0) {   // the leaf parents: column tt CPT + q
         const int tt = col / CPT, q = col & (CPT - 1);
         const int32_t p = q < C.KP ? S.idx[tt * k + C.sbP + q] : -1;
         index_bitmaps(P, lane, p, P.nt, S.cw);
@@ -97,7 +104,7 @@ __device__ __forceinline__ void col_scores(const ColPlan& C, const DevPlan& P, c
 // The backward of plans that decode through parent columns (P.wave_tokens =
 // 16 / CPT): grad_coef as in decode_bwd2_kernel, then the column decode of it.
 template <int CPT, int NG, bool G_BF16, bool GX_BF16>
-__global__ __launch_bounds__(kColThreads, 4) void col_bwd_kernel(ColPlan C, DevPlan P, const int32_t* __restrict__ idx,
+__global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT)) void col_bwd_kernel(ColPlan C, DevPlan P, const int32_t* __restrict__ idx,
                                                                  const void* __restrict__ g, int64_t T,
                                                                  float* __restrict__ grad_coef, void* grad_x,
                                                                  const float* __restrict__ add_gc, const void* add_gx,
@@ -107,7 +114,7 @@ __global__ __launch_bounds__(kColThreads, 4) void col_bwd_kernel(ColPlan C, DevP
     extern __shared__ __align__(16) unsigned char smem[];
     col_load_shared(C, smem);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const unsigned act_bytes = col_act_bytes(P, G_BF16);
+    const unsigned act_bytes = col_act_bytes(P, CPT, G_BF16);
     ColWave W = col_wave(C, smem, CPT, act_bytes, wave, lane);
     Wave S{};
     {
@@ -119,7 +126,7 @@ __global__ __launch_bounds__(kColThreads, 4) void col_bwd_kernel(ColPlan C, DevP
         S.pairs = (uint32_t*)(b + L.act);
         S.gf = (float*)(b + L.act);
         S.cw = (uint32_t*)(b + L.act + col_act_rows(P, G_BF16));
-        S.score = (float*)(b + L.act + col_act_rows(P, G_BF16) + align16u(16u * P.cws * 4u));
+        S.score = (float*)(b + L.act + col_act_rows(P, G_BF16) + (CPT ? col_act_bitmaps(P, CPT) : 0u));
     }
     const int nslots = TPW * C.k, d = C.d, dp = C.dp;
     const int64_t ngroups = (T + TPW - 1) / TPW, gstride = (int64_t)gridDim.x * kColWaves;
@@ -220,7 +227,7 @@ static void launch_colb_v(const ColPlan& C, const DevPlan& P, size_t lds, hipStr
                           const void* g, int64_t T, float* gc, void* gx, BwdExtra ex)
 {
     allow_lds(col_bwd_kernel<CPT, NG, GB, XB>, lds);
-    hipLaunchKernelGGL((col_bwd_kernel<CPT, NG, GB, XB>), col_grid(T, col_tpw(CPT), lds, 4, 1), dim3(kColThreads), lds,
+    hipLaunchKernelGGL((col_bwd_kernel<CPT, NG, GB, XB>), col_grid(T, col_tpw(CPT), lds, col_bwd_waves(CPT), 1), dim3(kColThreads), lds,
                        stream, C, P, idx, g, T, gc, gx, ex.gc, ex.gx, ex.stats);
 }
 
@@ -243,15 +250,16 @@ static bool launch_colb(const DevPlan& Pp, const int32_t* idx, const void* g, in
                            BwdExtra ex, hipStream_t stream)
 {
     const int cpt = col_cpt(Pp);
-    if (!cpt) return false;
+    if (cpt < 0) return false;
     DevPlan P = Pp;
     P.wave_tokens = col_tpw(cpt);
     const ColPlan C = col_plan(P, cpt);
     const size_t lds =
-        col_shared_bytes(C) + (size_t)kColWaves * col_layout(C, cpt, col_act_bytes(P, GB)).bytes;
+        col_shared_bytes(C) + (size_t)kColWaves * col_layout(C, cpt, col_act_bytes(P, cpt, GB)).bytes;
     if (lds > (size_t)kLdsBudget) return false;
     const int ng = ng_variant(P);
-    if (cpt == 4) launch_colb_ng<4, GB, XB>(ng, C, P, lds, stream, idx, g, T, gc, gx, ex);
+    if (cpt == 0) launch_colb_ng<0, GB, XB>(ng, C, P, lds, stream, idx, g, T, gc, gx, ex);
+    else if (cpt == 4) launch_colb_ng<4, GB, XB>(ng, C, P, lds, stream, idx, g, T, gc, gx, ex);
     else if (cpt == 8) launch_colb_ng<8, GB, XB>(ng, C, P, lds, stream, idx, g, T, gc, gx, ex);
     else launch_colb_ng<16, GB, XB>(ng, C, P, lds, stream, idx, g, T, gc, gx, ex);
     return true;

@@ -25,19 +25,19 @@ struct ActTile {
     const float* f;         // fp32: [TPW][dp]
 };
 
-// Words w0 + 4 m, m < MW, of the sign bitmap of index pu, two nibble groups at
-// a time: the XOR of one table row per group (parity is linear in the index
+// Words 4 m, m < MW, of the sign bitmap of index pu (from the table row nt of
+// the first of them), two nibble groups at a time: the XOR of one table row per group (parity is linear in the index
 // bits; table layout [g][w][16]: word w of group g for nibble value v at
 // (g * nchunk + w) * 16 + v).  Every read has a fixed offset from its group's
 // address and each pair of groups folds in one instruction a word.
 template <int MW>
-__device__ __forceinline__ void bitmap_words(const uint32_t* nt, int nchunk, int groups, uint32_t pu, bool live, int w0,
+__device__ __forceinline__ void bitmap_words(const uint32_t* nt, int nchunk, int groups, uint32_t pu, bool live,
                                              uint32_t* dst)
 {
     uint32_t acc[MW];
 #pragma unroll
     for (int m = 0; m < MW; ++m) acc[m] = 0;
-    const uint32_t* row = nt + w0 * 16;
+    const uint32_t* row = nt;
     int g = 0;
     for (; g + 1 < groups; g += 2) {
         const uint32_t* r0 = row + (pu & 15u);
@@ -59,7 +59,7 @@ __device__ __forceinline__ void bitmap_words(const uint32_t* nt, int nchunk, int
 // Sign bitmaps of sixteen columns into cw[16][cws] (bit b of word w = sign at
 // coordinate 32w + b), lane (col, w0) giving index p of column col = lane & 15
 // (zero words for p < 0) and building words w0, w0 + 4, ....  Rows of whole
-// quadruples of up to 32 words take bitmap_words (the parents' bitmaps were
+// quadruples of words take bitmap_words (the parents' bitmaps were
 // 130 of the encoder's 3,866 vector instructions per level and group, 18 for
 // each nibble group); the rest read clamped words.
 __device__ __forceinline__ void index_bitmaps(const DevPlan& P, int lane, int32_t p, const uint32_t* nt, uint32_t* cw)
@@ -67,17 +67,21 @@ __device__ __forceinline__ void index_bitmaps(const DevPlan& P, int lane, int32_
     const int nchunk = P.nchunk, w0 = lane >> 4, col = lane & 15;
     const uint32_t pu = p >= 0 ? (uint32_t)p : 0u;
     uint32_t* dst = cw + col * P.cws;
-    if ((nchunk & 3) == 0 && nchunk <= 32) {
-        switch (nchunk >> 2) {
-        case 1: return bitmap_words<1>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
-        case 2: return bitmap_words<2>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
-        case 3: return bitmap_words<3>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
-        case 4: return bitmap_words<4>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
-        case 5: return bitmap_words<5>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
-        case 6: return bitmap_words<6>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
-        case 7: return bitmap_words<7>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
-        default: return bitmap_words<8>(nt, nchunk, P.nt_groups, pu, p >= 0, w0, dst + w0);
+    if ((nchunk & 3) == 0) {
+        for (int wb = w0; wb < nchunk; wb += 32) {
+            const uint32_t* t = nt + 16 * wb;
+            switch (min(nchunk - wb + w0, 32) >> 2) {
+            case 1: bitmap_words<1>(t, nchunk, P.nt_groups, pu, p >= 0, dst + wb); break;
+            case 2: bitmap_words<2>(t, nchunk, P.nt_groups, pu, p >= 0, dst + wb); break;
+            case 3: bitmap_words<3>(t, nchunk, P.nt_groups, pu, p >= 0, dst + wb); break;
+            case 4: bitmap_words<4>(t, nchunk, P.nt_groups, pu, p >= 0, dst + wb); break;
+            case 5: bitmap_words<5>(t, nchunk, P.nt_groups, pu, p >= 0, dst + wb); break;
+            case 6: bitmap_words<6>(t, nchunk, P.nt_groups, pu, p >= 0, dst + wb); break;
+            case 7: bitmap_words<7>(t, nchunk, P.nt_groups, pu, p >= 0, dst + wb); break;
+            default: bitmap_words<8>(t, nchunk, P.nt_groups, pu, p >= 0, dst + wb); break;
+            }
         }
+        return;
     }
     constexpr int MW = 4;
     for (int wb = 0; wb < nchunk; wb += 4 * MW) {

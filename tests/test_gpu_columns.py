@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 
 DEV = "cuda:0"
 
-# name: (d, level bits, K per level); 16 children per parent
+# name: (d, level bits, K per level[, children per parent, else 16])
 PLANS = {
     "cpt8": (768, (10, 12, 15, 17, 20), (8, 8, 8, 8, 64)),
     "cpt4_d200": (200, (8, 10, 12), (4, 4, 8)),
@@ -33,7 +33,20 @@ PLANS = {
     "many_words": (512, (9, 11, 13, 15, 17, 19, 21, 23), (12, 12, 12, 12, 12, 12, 9, 18)),
     "beam24": (384, (9, 12, 15, 18), (24, 24, 8, 32)),       # 24 summed slots: all six groups of word 0
     "wide_code": (768, (10, 14, 18), (16, 16, 256)),
+    # no leaf columns: every hashed slot through the tables
+    "table_2l": (1024, (10, 15), (16, 32), 256),
+    "table_3l": (1024, (10, 15, 17), (16, 32, 64), 256),
+    "table_d2048": (2048, (11, 15), (16, 32), 256),
+    "table_d522": (522, (10, 13, 16), (8, 8, 16), 32),
+    "table_d64": (64, (6, 9), (3, 5), 16),
+    "table_odd": (333, (9, 13, 17), (16, 16, 16), 16),       # 32 slots: one full word
+    "table_254": (512, (9, 13, 17), (16, 110, 128), 64),     # the widest code of marks
+    "one_level": (300, (9,), (20,), 16),
 }
+
+
+def branch(name):
+    return PLANS[name][3] if len(PLANS[name]) > 3 else 16
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -45,9 +58,9 @@ def _gpu():
 
 def codes(name, T, seed):
     """Codes of random children (the layout of the encoder's), then one oddity per row."""
-    d, nb, K = PLANS[name]
+    d, nb, K = PLANS[name][:3]
     L, rng = len(nb), np.random.default_rng(seed)
-    dl = [0] + [16] * (L - 1)
+    dl = [0] + [branch(name)] * (L - 1)
     gens = oracle.generators(list(nb), dl, 0)
     base = np.concatenate([[0], np.cumsum(K)]).astype(int)
     idx = np.full((T, sum(K)), -1, np.int32)
@@ -62,17 +75,17 @@ def codes(name, T, seed):
     coef = rng.standard_normal(idx.shape).astype(np.float32)
     coef[idx < 0] = 0.0
     k, N = sum(K), 1 << nb[-1]
-    rand = lambda: int(rng.integers(d, N))
+    rand = lambda: int(rng.integers(d, N)) if d < N else 0
     odd = {
         1: lambda r: r.__setitem__(k - 1, rand()),                            # routes to no parent
         2: lambda r: r.__setitem__(1, r[0]),                                  # a basis slot twice
         3: lambda r: r.__setitem__(slice(base[L - 1], k), r[base[L - 1]]),    # one leaf in every leaf slot
         4: lambda r: r.__setitem__(0, r[k - 1]),                              # a hashed index on level 0
         5: lambda r: r.__setitem__(k - 1, r[0]),                              # a basis index among the leaves
-        6: lambda r: r.__setitem__(base[L - 2], rand() if L > 2 else r[1]),   # another parent: its children route nowhere
+        6: lambda r: r.__setitem__(base[max(L - 2, 0)], rand() if L > 2 else r[1]),   # another parent: its children route nowhere
         7: lambda r: r.__setitem__(slice(0, k), -1),                          # all padding
         8: lambda r: r.__setitem__(slice(0, k), rng.integers(0, N, k)),       # any indices
-        9: lambda r: r.__setitem__(slice(base[L - 2], base[L - 2] + 2), -1),  # padding parents
+        9: lambda r: r.__setitem__(slice(base[max(L - 2, 0)], base[max(L - 2, 0)] + 2), -1),  # padding parents
         10: lambda r: r.__setitem__(slice(0, k), rng.integers(0, d, k)),      # basis indices everywhere, repeated
     }
     for t, f in odd.items():
@@ -83,11 +96,11 @@ def codes(name, T, seed):
 
 @pytest.mark.parametrize("name", list(PLANS))
 def test_column_decode_and_bwd(name):
-    d, nb, K = PLANS[name]
+    d, nb, K = PLANS[name][:3]
     T = 23                                       # ragged last group for 2 and 4 tokens per wave
     print(f"[columns] {name} d={d} T={T}", flush=True)
     sys.stdout.flush()
-    plan = dpb.Plan(d, seed=0, level_bits=list(nb), branchings=[0] + [16] * (len(nb) - 1), active=list(K))
+    plan = dpb.Plan(d, seed=0, level_bits=list(nb), branchings=[0] + [branch(name)] * (len(nb) - 1), active=list(K))
     m = oracle.masks(d, nb[-1])
     idx, coef = codes(name, T, 9000 + d)
     di, dc = torch.from_numpy(idx).to(DEV), torch.from_numpy(coef).to(DEV)
