@@ -885,21 +885,8 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
         // fp32 activations: each value split exactly into three bf16 terms
         u32x4 bh[4], bm[4], bl[4];
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            const int tt = btok[n];
-            const uint32_t wd = W.b[n];
-            uint32_t hi[8], mi[8], lo[8];
-#pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                const int off = 4 * kq + (x >> 1) + 16 * (x & 1);
-                float v = xf[tt * dp + 32 * c + off];
-                v = __uint_as_float(__float_as_uint(v) ^ (((wd >> off) & 1u) << 31));
-                split3(v, hi[x], mi[x], lo[x]);
-            }
-            bh[n] = u32x4{hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16)};
-            bm[n] = u32x4{mi[0] | (mi[1] << 16), mi[2] | (mi[3] << 16), mi[4] | (mi[5] << 16), mi[6] | (mi[7] << 16)};
-            bl[n] = u32x4{lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16)};
-        }
+        for (int n = 0; n < 4; ++n)
+            split_column(xf + btok[n] * dp + 32 * c + 4 * kq, rotl32(W.b[n], 15u - 4u * (uint32_t)kq), bh[n], bm[n], bl[n]);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const bf16x8 av = afrag(W.a[mt]);

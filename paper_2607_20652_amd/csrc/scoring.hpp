@@ -117,6 +117,33 @@ __device__ void column_bitmaps(const DevPlan& P, int lane, int ntok, int csh, in
     index_bitmaps(P, lane, p, nt, cw);
 }
 
+// The column operands of fp32 activations: dword i pairs coordinates i and
+// i + 16 from `f` on, split exactly into three bf16 terms (v = hi + mid + lo,
+// round to nearest even), with the signs of R's bits 15 and 31 rotated by i.
+// The pack conversion rounds two values at once and the signs go onto the
+// packed terms (the split is odd): 60 vector instructions, against 180 for
+// rounding in integer arithmetic value by value.
+__device__ __forceinline__ void split_column(const float* f, uint32_t R, u32x4& bh, u32x4& bm, u32x4& bl)
+{
+    const float4 a = *(const float4*)f, b = *(const float4*)(f + 16);
+    const float lo[4] = {a.x, a.y, a.z, a.w}, hi[4] = {b.x, b.y, b.z, b.w};
+    uint32_t h[4], m[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t s = (i ? __builtin_amdgcn_alignbit(R, R, i) : R);
+        h[i] = pack_bf16x2(lo[i], hi[i]);
+        const float r0 = lo[i] - __uint_as_float(h[i] << 16), r1 = hi[i] - __uint_as_float(h[i] & 0xFFFF0000u);
+        m[i] = pack_bf16x2(r0, r1);
+        l[i] = pack_bf16x2(r0 - __uint_as_float(m[i] << 16), r1 - __uint_as_float(m[i] & 0xFFFF0000u));
+        h[i] ^= s & 0x80008000u;
+        m[i] ^= s & 0x80008000u;
+        l[i] ^= s & 0x80008000u;
+    }
+    bh = u32x4{h[0], h[1], h[2], h[3]};
+    bm = u32x4{m[0], m[1], m[2], m[3]};
+    bl = u32x4{l[0], l[1], l[2], l[3]};
+}
+
 // Unscaled scores of generator tile mb for this lane's column (lane & 15):
 // acc[i] = S[16*mb + 4*(lane>>4) + i][column].  Columns without a parent
 // produce scores of row trow that the callers discard.
@@ -143,17 +170,8 @@ __device__ __forceinline__ void score_chunk2(int kq, u32x4 a, u32x4 one, uint32_
         b.w = pd.w ^ (__builtin_amdgcn_alignbit(R, R, 3) & 0x80008000u);
         product(b);
     } else {
-        uint32_t hi[8], mi[8], lo[8];
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            const int off = 4 * kq + (x >> 1) + 16 * (x & 1);
-            float v = frow[32 * c + off];
-            v = __uint_as_float(__float_as_uint(v) ^ (((wd >> off) & 1u) << 31));
-            split3(v, hi[x], mi[x], lo[x]);
-        }
-        const u32x4 bh = {hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16), hi[4] | (hi[5] << 16), hi[6] | (hi[7] << 16)};
-        const u32x4 bm = {mi[0] | (mi[1] << 16), mi[2] | (mi[3] << 16), mi[4] | (mi[5] << 16), mi[6] | (mi[7] << 16)};
-        const u32x4 bl = {lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16), lo[4] | (lo[5] << 16), lo[6] | (lo[7] << 16)};
+        u32x4 bh, bm, bl;
+        split_column(frow + 32 * c + 4 * kq, rotl32(wd, 15u - 4u * (uint32_t)kq), bh, bm, bl);
         product(bh);
         product(bm);
         product(bl);
