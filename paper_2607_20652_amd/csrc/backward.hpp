@@ -185,19 +185,6 @@ struct BwdExtra {
     const float2* stats;
 };
 
-inline int device_cus()
-{
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            cus = prop.multiProcessorCount;
-        if (cus <= 0) cus = 256;
-    }
-    return cus;
-}
-
 // Kernel variants: index groups NG in {3, 4, 5, 6, 8} (a larger NG than the
 // plan needs is exact: the extra table rows are zero) and the width of the
 // leaf parents' sign bits.

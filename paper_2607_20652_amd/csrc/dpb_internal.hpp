@@ -177,6 +177,20 @@ inline void allow_lds(F* kernel, size_t bytes)
         (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// Compute units of the current device (asked once: the answer sizes grids only).
+inline int device_cus()
+{
+    static int cus = 0;
+    if (!cus) {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
+            cus = prop.multiProcessorCount;
+        if (cus <= 0) cus = 256;
+    }
+    return cus;
+}
+
 // True when the general encoder's workgroup (one fp32 token) fits the LDS budget.
 bool general_encoder_fits(const DevPlan& P);
 

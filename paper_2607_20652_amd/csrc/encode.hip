@@ -53,18 +53,10 @@ __host__ __device__ inline int enc_r(const DevPlan& P)
     return 4 * pow2_ceil(mb);
 }
 
-__host__ __device__ inline EncLayout enc_layout(const DevPlan& P, bool act_bf16, bool std = false)
+__host__ __device__ inline EncLayout enc_layout_with(const DevPlan& P, bool act_bf16, int listn)
 {
     EncLayout L;
-    const int TPW = P.wave_tokens, LPT = 64 / TPW;
-    const int ND = (P.dp / 2 + LPT - 1) / LPT;  // activation dwords per lane at level 0
-    // level-0 candidates: the K_0 lanes whose maximum reaches tau, each with all
-    // its keys; listn counts 64-bit words per token.  Plain bf16 keys are 32
-    // bits (2 ND per lane, two to a word); standardized and fp32 keys are 64.
-    // The beam levels' selection keeps two keys per lane of a token there.
-    const int level0 = (act_bf16 && !std) ? P.active[0] * ND
-                                          : P.active[0] * (act_bf16 ? 2 * ND : (P.d + LPT - 1) / LPT);
-    const int listn = level0 > 2 * LPT ? level0 : 2 * LPT;
+    const int TPW = P.wave_tokens;
     L.listn = listn;
     L.kmaxp = P.kmax;
     unsigned off = 0;
@@ -78,11 +70,34 @@ __host__ __device__ inline EncLayout enc_layout(const DevPlan& P, bool act_bf16,
     return L;
 }
 
+// The least a wave needs: level-0 candidates, the K_0 lanes whose maximum
+// reaches tau, each with all its keys; listn counts 64-bit words per token.
+// Plain bf16 keys are 32 bits (2 ND per lane, two to a word); standardized
+// and fp32 keys are 64.
+inline EncLayout enc_layout_least(const DevPlan& P, bool act_bf16, bool std)
+{
+    const int LPT = 64 / P.wave_tokens;
+    const int ND = (P.dp / 2 + LPT - 1) / LPT;  // activation dwords per lane at level 0
+    return enc_layout_with(P, act_bf16,
+                           (act_bf16 && !std) ? P.active[0] * ND
+                                              : P.active[0] * (act_bf16 ? 2 * ND : (P.d + LPT - 1) / LPT));
+}
+
 // Shared LDS of an encoder workgroup: nibble tables, generators and, with
 // standardization, the level-0 statistics.
 __host__ __device__ inline unsigned enc_shared_bytes(const DevPlan& P, bool std)
 {
     return align16u(P.nt_groups * 16 * P.nchunk * 4) + align16u(P.gens_total * 4) + (std ? align16u(P.d * 8) : 0u);
+}
+
+// The layout in use: where the LDS holds it, lists of two keys per lane (the
+// beam levels' selection).
+inline EncLayout enc_layout(const DevPlan& P, bool act_bf16, bool std)
+{
+    const EncLayout least = enc_layout_least(P, act_bf16, std);
+    const int two = 2 * (64 / P.wave_tokens);
+    const EncLayout L = enc_layout_with(P, act_bf16, least.listn > two ? least.listn : two);
+    return enc_shared_bytes(P, std) + kEncWaves * L.bytes <= (unsigned)kLdsBudget ? L : least;
 }
 
 __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src)
@@ -407,7 +422,7 @@ __device__ void level0_std(const DevPlan& P, int lane, int64_t t0, int ntok, con
 // variant gains from it only because its level-0 list holds 32-bit keys at
 // half the 64-bit size, so that four workgroups fit the LDS of a CU.
 template <bool X_BF16, int CPT, int R, bool STD>
-__global__ __launch_bounds__(kEncThreads, (X_BF16 && (CPT == 16 || CPT == 8) && R == 4 && !STD) ? 4 : 1) void encode3_kernel(DevPlan P, const void* __restrict__ xin, int64_t T,
+__global__ __launch_bounds__(kEncThreads, (X_BF16 && (CPT == 16 || CPT == 8) && R == 4 && !STD) ? 4 : 1) void encode3_kernel(DevPlan P, int listn, const void* __restrict__ xin, int64_t T,
                                                               const float2* __restrict__ stats,
                                                               int32_t* __restrict__ out_idx,
                                                               float* __restrict__ out_coef)
@@ -429,7 +444,7 @@ __global__ __launch_bounds__(kEncThreads, (X_BF16 && (CPT == 16 || CPT == 8) && 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int d = P.d, dp = P.dp;
     const int x32 = (lane ^ 32) << 2;
-    const EncLayout EL = enc_layout(P, X_BF16, STD);
+    const EncLayout EL = enc_layout_with(P, X_BF16, listn);
     unsigned char* wb = smem + enc_shared_bytes(P, STD) + (unsigned)wave * EL.bytes;
     uint32_t* pairs = (uint32_t*)(wb + EL.act);
     float* xf = (float*)(wb + EL.act);
@@ -555,7 +570,7 @@ __global__ __launch_bounds__(kEncThreads, (X_BF16 && (CPT == 16 || CPT == 8) && 
             // 188 -> 171, standardized 367 -> 331.)
             const int Kl = P.active[l];
             bool done = false;
-            if (Kl <= 2 * CPT) {
+            if (Kl <= 2 * CPT && EL.listn >= 8 * CPT) {
                 uint32_t mg[R], top[1] = {0u};
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
@@ -1408,7 +1423,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_select_kernel(DevPlan P, in
 // Whether the standardized encoder's workgroup fits the LDS budget.
 bool encode2_std_supported(const DevPlan& P)
 {
-    const size_t lds = enc_shared_bytes(P, true) + (size_t)kEncWaves * enc_layout(P, false).bytes;
+    const size_t lds = enc_shared_bytes(P, true) + (size_t)kEncWaves * enc_layout_least(P, false, false).bytes;
     return encode2_supported(P) && lds <= (size_t)kLdsBudget;
 }
 
@@ -1419,7 +1434,7 @@ bool encode2_supported(const DevPlan& P)
     for (int l = 1; l < P.levels; ++l)
         if (P.cpt[l] > 16 || TPW * P.cpt[l] > 16) return false;
     if (16 / TPW != 4 && 16 / TPW != 8 && 16 / TPW != 16) return false;
-    const size_t lds = enc_shared_bytes(P, false) + (size_t)kEncWaves * enc_layout(P, false).bytes;
+    const size_t lds = enc_shared_bytes(P, false) + (size_t)kEncWaves * enc_layout_least(P, false, false).bytes;
     return lds <= (size_t)kLdsBudget;
 }
 
@@ -1427,13 +1442,12 @@ hipError_t launch_encode2(const DevPlan& P, const void* x, bool x_bf16, int64_t 
                           float* coef, hipStream_t stream)
 {
     const float2* st = (const float2*)stats;
-    const size_t lds = enc_shared_bytes(P, stats != nullptr) + (size_t)kEncWaves * enc_layout(P, x_bf16, stats != nullptr).bytes;
+    const EncLayout EL = enc_layout(P, x_bf16, stats != nullptr);
+    const int listn = EL.listn;
+    const size_t lds = enc_shared_bytes(P, stats != nullptr) + (size_t)kEncWaves * EL.bytes;
     const int64_t groups = (T + P.wave_tokens - 1) / P.wave_tokens;
     const int64_t need = (groups + kEncWaves - 1) / kEncWaves;
-    int cus = 256, dev = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-        cus = prop.multiProcessorCount;
+    const int cus = device_cus();
     const int per_cu = (int)std::max<size_t>(1, (160 * 1024) / std::max<size_t>(lds, 1));
     const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)cus * std::min(per_cu, 8) * 4)));
     const int R = enc_r(P), CPT = 16 / P.wave_tokens;
@@ -1441,11 +1455,11 @@ hipError_t launch_encode2(const DevPlan& P, const void* x, bool x_bf16, int64_t 
     do {                                                                                                           \
         if (st) {                                                                                                  \
             allow_lds(encode3_kernel<XB, CV, RV, true>, lds);                                                      \
-            hipLaunchKernelGGL((encode3_kernel<XB, CV, RV, true>), grid, dim3(kEncThreads), lds, stream, P, x, T,  \
+            hipLaunchKernelGGL((encode3_kernel<XB, CV, RV, true>), grid, dim3(kEncThreads), lds, stream, P, listn, x, T, \
                                st, idx, coef);                                                                     \
         } else {                                                                                                   \
             allow_lds(encode3_kernel<XB, CV, RV, false>, lds);                                                     \
-            hipLaunchKernelGGL((encode3_kernel<XB, CV, RV, false>), grid, dim3(kEncThreads), lds, stream, P, x, T, \
+            hipLaunchKernelGGL((encode3_kernel<XB, CV, RV, false>), grid, dim3(kEncThreads), lds, stream, P, listn, x, T, \
                                st, idx, coef);                                                                     \
         }                                                                                                          \
     } while (0)
@@ -1555,10 +1569,7 @@ hipError_t launch_encode_wide(const DevPlan& P, const void* x, bool x_bf16, int6
 {
     const float2* st = (const float2*)stats;
     {
-        int cus = 256, dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            cus = prop.multiProcessorCount;
+        const int cus = device_cus();
         const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>((T + 3) / 4, (int64_t)cus * 8)));
         const size_t lds = wide_level0_lds(P, x_bf16, st != nullptr);
 #define DPB_W0(XB, SD)                                                                                        \
