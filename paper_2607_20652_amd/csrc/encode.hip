@@ -24,6 +24,7 @@
 //    in order.
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "scoring.hpp"
 
@@ -845,20 +846,31 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
         const int col = threadIdx.x & (kWideCols - 1), tt = col >> csh, q = col & (KC - 1);
         const int32_t p = (tt < nt_tok && q < KP) ? idx[(t0 + tb + tt) * P.k_tot + P.slot_base[l - 1] + q] : -1;
         if (threadIdx.x < kWideCols) s_pidx[col] = p;
-        // all kNtGroupsPadded groups are read (zero words past nt_groups): the
-        // loads of a word are independent and wait once
+        // the loads of a word are independent and wait once; only the index's
+        // own groups are read, two folded per instruction
         const uint32_t pu = p >= 0 ? (uint32_t)p : 0u;
-        uint32_t toff[kNtGroupsPadded];
-#pragma unroll
-        for (int g = 0; g < kNtGroupsPadded; ++g) toff[g] = 4u * ((uint32_t)(g * nchunk * 16) + ((pu >> (4 * g)) & 15u));
         const unsigned char* ntb = (const unsigned char*)P.nt;
-#pragma unroll 2
-        for (int w = threadIdx.x / kWideCols; w < nchunk; w += kWideThreads / kWideCols) {
-            uint32_t word = 0;
+        auto words = [&](auto groups) {
+            constexpr int NG = groups.value;
+            uint32_t toff[NG];
 #pragma unroll
-            for (int g = 0; g < kNtGroupsPadded; ++g) word ^= *(const uint32_t*)(ntb + toff[g] + (uint32_t)w * 64u);
-            cw[col * P.cws + w] = p >= 0 ? word : 0u;
-        }
+            for (int g = 0; g < NG; ++g) toff[g] = 4u * ((uint32_t)(g * nchunk * 16) + ((pu >> (4 * g)) & 15u));
+#pragma unroll 4
+            for (int w = threadIdx.x / kWideCols; w < nchunk; w += kWideThreads / kWideCols) {
+                uint32_t t[NG];
+#pragma unroll
+                for (int g = 0; g < NG; ++g) t[g] = *(const uint32_t*)(ntb + toff[g] + (uint32_t)w * 64u);
+                uint32_t word = __builtin_amdgcn_bitop3_b32(t[0], t[1], t[2], 0x96);
+#pragma unroll
+                for (int g = 3; g + 1 < NG; g += 2) word = __builtin_amdgcn_bitop3_b32(word, t[g], t[g + 1], 0x96);
+                if constexpr (NG % 2 == 0) word ^= t[NG - 1];
+                cw[col * P.cws + w] = p >= 0 ? word : 0u;
+            }
+        };
+        if (P.nt_groups <= 3) words(std::integral_constant<int, 3>{});
+        else if (P.nt_groups == 4) words(std::integral_constant<int, 4>{});
+        else if (P.nt_groups == 5) words(std::integral_constant<int, 5>{});
+        else words(std::integral_constant<int, kNtGroupsPadded>{});
     }
     __syncthreads();
 
