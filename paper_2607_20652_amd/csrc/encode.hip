@@ -972,20 +972,25 @@ __global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2)
         // one chunk: cur = its column operands, a = its row words, an = those
         // of the next chunk (its first row operand is built here)
         auto chunk = [&](int c, u32x4 (&cur)[4], u32x4 (&next)[4], uint32_t (&a)[MT], uint32_t (&an)[MT]) {
-            const int cf = min(c + 2, nchunk - 1);
+            const int cf = c + 2;   // past the last chunk: words of the next row, never used
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
                 for (int n = 0; n < 4; ++n) {
-                    const int s = 4 * mt + n;
                     acc[mt][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                         __builtin_bit_cast(bf16x8, av[mt & 1]), __builtin_bit_cast(bf16x8, cur[n]), acc[mt][n], 0, 0, 0);
-                    row_op(n, mt + 1 < MT ? a[mt + 1 < MT ? mt + 1 : 0] : an[0], av[(mt + 1) & 1]);
+                    // the row operand is done two slots before it is used
+                    const uint32_t w = mt + 1 < MT ? a[mt + 1 < MT ? mt + 1 : 0] : an[0];
+                    if (n == 0) row_op(0, w, av[(mt + 1) & 1]);
+                    if (n < 3) row_op(n + 1, w, av[(mt + 1) & 1]);
+                    const int first = n == 0 ? 0 : n - 1, count = n == 0 ? 0 : n == 3 ? 2 : 1;   // of the tile's four shares
 #pragma unroll
-                    for (int u = 0; u < BPS; ++u) {
-                        const int k = s * BPS + u;
-                        col_op(k & 7, bw[k >> 3], pd[k >> 3], next[k >> 3]);
-                        if ((k & 7) == 7) fetch_col(cf, k >> 3);
+                    for (int u = 0; u < 2 * BPS; ++u) {
+                        const int k = (4 * mt + first) * BPS + u;
+                        if (u < count * BPS) {
+                            col_op(k & 7, bw[k >> 3], pd[k >> 3], next[k >> 3]);
+                            if ((k & 7) == 7) fetch_col(cf, k >> 3);
+                        }
                     }
                     if (n == 3) fetch_row(cf, mt, a);
                     __builtin_amdgcn_sched_barrier(0);
