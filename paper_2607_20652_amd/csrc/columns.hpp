@@ -71,7 +71,7 @@ constexpr int kColWaves = 4;
 constexpr int kColThreads = 64 * kColWaves;
 // Waves per SIMD the kernels are held to by registers.
 constexpr int col_decode_waves(int cpt) { return cpt ? 4 : 8; }
-constexpr int col_bwd_waves(int cpt) { return cpt ? 4 : 5; }
+constexpr int col_bwd_waves(int cpt, bool g_bf16) { return cpt == 0 && g_bf16 ? 5 : 4; }   // (five in fp32: 60 us for 53)
 constexpr int kColMaxSlots = 254;   // a mark holds slot + 1 in a byte
 
 // CPT = 0: a plan without leaf columns.  One token per wave, every hashed slot

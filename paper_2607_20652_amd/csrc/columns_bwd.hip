@@ -104,7 +104,7 @@ __device__ __forceinline__ void col_scores(const ColPlan& C, const DevPlan& P, c
 // The backward of plans that decode through parent columns (P.wave_tokens =
 // 16 / CPT): grad_coef as in decode_bwd2_kernel, then the column decode of it.
 template <int CPT, int NG, bool G_BF16, bool GX_BF16>
-__global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT)) void col_bwd_kernel(ColPlan C, DevPlan P, const int32_t* __restrict__ idx,
+__global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT, G_BF16)) void col_bwd_kernel(ColPlan C, DevPlan P, const int32_t* __restrict__ idx,
                                                                  const void* __restrict__ g, int64_t T,
                                                                  float* __restrict__ grad_coef, void* grad_x,
                                                                  const float* __restrict__ add_gc, const void* add_gx,
@@ -143,8 +143,26 @@ __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT)) void col_bwd_kerne
             nidx[e] = i < n ? pi[i] : -1;
         }
     };
+    // and so are its bf16 gradient rows for two and four tokens a wave, where
+    // four pieces of 512 coordinates hold them (65,536 tokens d 768 285 -> 277
+    // us, 20,000 tokens d 200 26.6 -> 23.5; with one token a wave the table
+    // reads, more of them per row, wait behind the requested rows: d 1024
+    // N 2^24 183 -> 187, pt_large_2l 82 -> 93)
+    constexpr bool kRows = G_BF16 && TPW > 1;
+    constexpr int kPieces = 4, PPT = kPieces / TPW;
+    const bool pfg = kRows && d <= 512 * PPT && (d & 7) == 0;
+    u32x4 ng[kPieces];
+    auto fetch_g = [&](int64_t gp) {
+#pragma unroll
+        for (int e = 0; e < kPieces; ++e) {
+            const int o = (e % PPT) * 512 + lane * 8;
+            const int64_t t = gp * TPW + e / PPT;
+            ng[e] = (o < d && t < T) ? *(const u32x4*)((const uint16_t*)g + t * d + o) : u32x4{0u, 0u, 0u, 0u};
+        }
+    };
     int64_t grp = (int64_t)blockIdx.x * kColWaves + wave;
     if (pf && grp < ngroups) fetch(grp);
+    if (pfg && grp < ngroups) fetch_g(grp);
     for (; grp < ngroups; grp += gstride) {
         const int64_t t0 = grp * TPW;
         W.ntok = S.ntok = (int)min((int64_t)TPW, T - t0);
@@ -164,7 +182,14 @@ __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT)) void col_bwd_kerne
         } else {
             for (int i = ln; i < nslots; i += 64) W.idx[i] = i < n ? idx[grp * nslots + i] : -1;
         }
-        if constexpr (G_BF16) {
+        if (kRows && pfg) {
+#pragma unroll
+            for (int e = 0; e < kPieces; ++e) {
+                const int o = (e % PPT) * 512 + ln * 8;
+                if (o < dp) store_pair_piece(ln, ng[e], o, S.pairs + (e / PPT) * P.prow);
+            }
+            if (grp + gstride < ngroups) fetch_g(grp + gstride);
+        } else if constexpr (G_BF16) {
             load_pairs(P, ln, W.ntok, TPW, (const uint16_t*)g, t0, S.pairs);
         } else {
             const float* gfp = (const float*)g;
@@ -227,7 +252,7 @@ static void launch_colb_v(const ColPlan& C, const DevPlan& P, size_t lds, hipStr
                           const void* g, int64_t T, float* gc, void* gx, BwdExtra ex)
 {
     allow_lds(col_bwd_kernel<CPT, NG, GB, XB>, lds);
-    hipLaunchKernelGGL((col_bwd_kernel<CPT, NG, GB, XB>), col_grid(T, col_tpw(CPT), lds, col_bwd_waves(CPT), 1), dim3(kColThreads), lds,
+    hipLaunchKernelGGL((col_bwd_kernel<CPT, NG, GB, XB>), col_grid(T, col_tpw(CPT), lds, col_bwd_waves(CPT, GB), 1), dim3(kColThreads), lds,
                        stream, C, P, idx, g, T, gc, gx, ex.gc, ex.gx, ex.stats);
 }
 
