@@ -144,10 +144,9 @@ __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT, G_BF16)) void col_b
         }
     };
     // and so are its bf16 gradient rows for two and four tokens a wave, where
-    // four pieces of 512 coordinates hold them (65,536 tokens d 768 285 -> 277
-    // us, 20,000 tokens d 200 26.6 -> 23.5; with one token a wave the table
-    // reads, more of them per row, wait behind the requested rows: d 1024
-    // N 2^24 183 -> 187, pt_large_2l 82 -> 93)
+    // four pieces of 512 coordinates hold them (65,536 tokens d 768 285 -> 274
+    // us, 20,000 tokens d 200 26.6 -> 23.2; one token a wave measured slower
+    // with it: d 1024 N 2^24 183 -> 186, pt_large_2l 82 -> 103)
     constexpr bool kRows = G_BF16 && TPW > 1;
     constexpr int kPieces = 4, PPT = kPieces / TPW;
     const bool pfg = kRows && d <= 512 * PPT && (d & 7) == 0;
@@ -178,7 +177,6 @@ __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT, G_BF16)) void col_b
                 const int i = e * 64 + ln;
                 if (i < nslots) W.idx[i] = nidx[e];
             }
-            if (grp + gstride < ngroups) fetch(grp + gstride);
         } else {
             for (int i = ln; i < nslots; i += 64) W.idx[i] = i < n ? idx[grp * nslots + i] : -1;
         }
@@ -188,7 +186,6 @@ __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT, G_BF16)) void col_b
                 const int o = (e % PPT) * 512 + ln * 8;
                 if (o < dp) store_pair_piece(ln, ng[e], o, S.pairs + (e / PPT) * P.prow);
             }
-            if (grp + gstride < ngroups) fetch_g(grp + gstride);
         } else if constexpr (G_BF16) {
             load_pairs(P, ln, W.ntok, TPW, (const uint16_t*)g, t0, S.pairs);
         } else {
@@ -238,6 +235,12 @@ __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT, G_BF16)) void col_b
                 if (c >= 0 && (c >> nfeat_sh) == 0) W.coef[i] *= stats[c].y;
             }
             wave_sync();
+        }
+        // requested here, after the scoring's table reads: memory waits are in
+        // issue order, and the decode's set-up reads no memory
+        if (grp + gstride < ngroups) {
+            if (pf) fetch(grp + gstride);
+            if (kRows && pfg) fetch_g(grp + gstride);
         }
         // grad_x = decode(idx, grad_coef) (+ add_gx); the scoring buffers are dead now
         col_alpha<CPT>(C, W, W.coef, [&](int tt, int s) { return S.route[tt * C.k + s]; });
