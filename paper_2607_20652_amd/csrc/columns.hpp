@@ -339,8 +339,9 @@ __device__ __forceinline__ void col_tables(const ColPlan& C, const ColWave& W, c
 // Marks the basis slots' coordinates with slot + 1 and keeps their
 // coefficients by mark in W.bas (a coordinate held by several slots gathers
 // their coefficients in the marked one); lists the slots to be added one by
-// one and returns the largest number of them any token has.  (Leaf slots that
-// went into their parent's column hold index -1 by now.)
+// one and returns the largest number of them any token has, negative when
+// only their slot numbers are listed.  (Leaf slots that went into their
+// parent's column hold index -1 by now.)
 template <int CPT>
 __device__ __forceinline__ int col_marks(const ColPlan& C, const ColWave& W, const float* cf)
 {
@@ -385,6 +386,17 @@ __device__ __forceinline__ int col_marks(const ColPlan& C, const ColWave& W, con
         }
         for (int i = n + lane; i < k; i += 64) W.xs[tt * k + i] = 0xFFFF;   // no slot
         most = max(most, n);
+    }
+    wave_sync();
+    constexpr int cap = 64 / TPW;
+    if (most > cap) return -most;
+    // few (an edited code has a handful): index and scaled coefficient of
+    // each, zero past the last, where the tables' scratch is free by now
+    {
+        const int i = lane & (cap - 1), tt = lane / cap, s = i < most ? W.xs[tt * k + i] : 0xFFFF;
+        const int at = tt * k + (s == 0xFFFF ? 0 : s);
+        const float a = s == 0xFFFF ? 0.f : C.rsd * cf[at];
+        ((u32x2*)W.scr)[lane] = u32x2{(uint32_t)W.idx[at], __float_as_uint(a)};
     }
     wave_sync();
     return most;
@@ -549,13 +561,21 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
         if (nx) {
             // slots added one by one: sign = parity of the row mask and the index
             const uint32_t M0 = (s0[0] >> 2) | (s1[0] << 2), M1 = (s0[1] >> 2) | (s1[1] << 2);
-            for (int i = 0; i < nx; ++i) {
-                const int s = W.xs[tt * C.k + i];
-                const int at = tt * C.k + (s == 0xFFFF ? 0 : s);
-                const float a = s == 0xFFFF ? 0.f : C.rsd * cf[at];
-                const uint32_t c = (uint32_t)W.idx[at];
+            auto add_slot = [&](uint32_t c, float a) {
                 y[0] += signed_by_parity(a, M0 & c);
                 y[1] += signed_by_parity(a, M1 & c);
+            };
+            const u32x2* few = (const u32x2*)W.scr + tt * (64 / TPW);
+            for (int i = 0; i < nx; i += 4) {
+                u32x2 q[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) q[u] = few[i + u];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) add_slot(q[u].x, __uint_as_float(q[u].y));
+            }
+            for (int i = 0; i < -nx; ++i) {
+                const int s = W.xs[tt * C.k + i], at = tt * C.k + (s == 0xFFFF ? 0 : s);
+                add_slot((uint32_t)W.idx[at], s == 0xFFFF ? 0.f : C.rsd * cf[at]);
             }
         }
         if (m * 2 * LPT < lim) {
