@@ -56,7 +56,9 @@ def kernel_source_digest() -> str:
     return h.hexdigest()[:16]
 
 
-KERNEL_SYMBOLS = {"encode": "encode3_kernel", "decode": "decode2_kernel", "decode_bwd": "decode_bwd2_kernel"}
+# kernels of each step (the second: codes wider than 254 slots)
+KERNEL_SYMBOLS = {"encode": ("encode3_kernel",), "decode": ("col_decode_kernel", "decode2_kernel"),
+                  "decode_bwd": ("col_bwd_kernel", "decode_bwd2_kernel")}
 
 
 def ingest_counters(fetch_csv: str, write_csv: str, workload: str) -> dict:
@@ -72,8 +74,8 @@ def ingest_counters(fetch_csv: str, write_csv: str, workload: str) -> dict:
                 continue
             name = r["Kernel_Name"]
             key = "copy"  # runtime copies and fills
-            for k, sym in KERNEL_SYMBOLS.items():
-                if sym in name:
+            for k, symbols in KERNEL_SYMBOLS.items():
+                if any(sym in name for sym in symbols):
                     key = k
             acc.setdefault(key, []).append(float(r["Counter_Value"]) * 1024.0)
         if not acc.get("copy"):
