@@ -22,6 +22,9 @@ __host__ __device__ inline unsigned col_act_bytes(const DevPlan& P, int cpt, boo
     return col_act_rows(P, g_bf16) + col_act_bitmaps(P, cpt) + (cpt ? 1024u : 0u);
 }
 
+// The smallest fp32 magnitude (bits) that rounds to an infinite bf16.
+constexpr uint32_t kBf16Inf = 0x7F7F8000u;
+
 // Unscaled sums of one block of sixteen columns phi~_p (.) g against the
 // level's sixteen generators (LEAF: `s`, the child scores, lane rows 4 kq ..)
 // and against ones (`o`, the column's own <phi~_p, g>, the same in every row).
@@ -64,7 +67,10 @@ __device__ __forceinline__ void column_products(const DevPlan& P, const Wave& S,
 // direct reductions, so the summed slots are left to those.)  Measured, us:
 // 65,536 tokens d 768 k 96 304 -> 299, 8,192 tokens d 768 k 56 37 -> 35,
 // 16,381 tokens d 1024 k 144 191 -> 187, 20,000 tokens d 200 k 16 31 -> 27,
-// 8,192 tokens d 768 k 56 in fp32 85 -> 74.
+// 8,192 tokens d 768 k 56 in fp32 85 -> 74.  An fp32 gradient whose high
+// term is infinite has no such split (inf - inf in the second term): the
+// parents of a token that holds one are reduced directly, which gives the
+// signed infinity, or the finite sum of a value beyond the largest bf16.
 template <int CPT, bool G_BF16>
 __device__ __forceinline__ void col_scores(const ColPlan& C, const DevPlan& P, const Wave& S)
 {
@@ -180,6 +186,7 @@ __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT, G_BF16)) void col_b
         } else {
             for (int i = ln; i < nslots; i += 64) W.idx[i] = i < n ? idx[grp * nslots + i] : -1;
         }
+        uint32_t nosplit = 0;   // tokens with a gradient value that has no three-term split
         if (kRows && pfg) {
 #pragma unroll
             for (int e = 0; e < kPieces; ++e) {
@@ -190,9 +197,15 @@ __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT, G_BF16)) void col_b
             load_pairs(P, ln, W.ntok, TPW, (const uint16_t*)g, t0, S.pairs);
         } else {
             const float* gfp = (const float*)g;
-            for (int tt = 0; tt < TPW; ++tt)
-                for (int iota = ln; iota < dp; iota += 64)
-                    S.gf[tt * dp + iota] = (tt < W.ntok && iota < d) ? gfp[(t0 + tt) * d + iota] : 0.f;
+            for (int tt = 0; tt < TPW; ++tt) {
+                uint32_t top = 0;
+                for (int iota = ln; iota < dp; iota += 64) {
+                    const float v = (tt < W.ntok && iota < d) ? gfp[(t0 + tt) * d + iota] : 0.f;
+                    S.gf[tt * dp + iota] = v;
+                    top = max(top, __float_as_uint(v) & 0x7FFFFFFFu);
+                }
+                nosplit |= (uint32_t)(__ballot(top >= kBf16Inf) != 0) << tt;
+            }
         }
         wave_sync();
         col_parents<CPT>(C, W);
@@ -208,7 +221,7 @@ __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT, G_BF16)) void col_b
             W.coef[i] = v;
             int rt = -1;
             if (s >= C.sbL) rt = c >= d ? col_route<CPT>(C, W, tt, (uint32_t)c) : -1;
-            else if (s >= C.sbP || (G_BF16 && s >= C.ss)) rt = 0;   // taken as a column of its own
+            else if ((s >= C.sbP || (G_BF16 && s >= C.ss)) && !((nosplit >> tt) & 1u)) rt = 0;   // a column of its own
             S.route[i] = rt;
             direct |= c >= d && rt < 0;
         }

@@ -120,3 +120,31 @@ def test_column_decode_and_bwd(name):
             buf = add.to(DEV)
             _, gx2 = dpb.decode_bwd_ex(plan, di, g.to(DEV), add_grad_x=buf, grad_x=buf)
             compare_dense(gx2.float().cpu().numpy(), rgx + add.double().numpy(), tol)
+
+
+@pytest.mark.parametrize("name", ["cpt8", "cpt4_d200", "cpt16", "odd_d"])
+def test_infinite_fp32_gradient_reaches_the_parents_signed(name):
+    """An fp32 gradient that is infinite, or finite beyond the largest bf16, has
+    no split into bf16 terms: the parents' coefficients are the signed infinity
+    (or the finite sum), as the definition gives, and other rows stay within tolerance."""
+    d, nb, K = PLANS[name][:3]
+    T = 23
+    print(f"[infinite gradient] {name}", flush=True)
+    plan = dpb.Plan(d, seed=0, level_bits=list(nb), branchings=[0] + [branch(name)] * (len(nb) - 1), active=list(K))
+    m = oracle.masks(d, nb[-1])
+    idx, _ = codes(name, T, 9300 + d)
+    di = torch.from_numpy(idx).to(DEV)
+    g = inputs.normal((T, d), 9400 + d, "f32")
+    g[12, 3] = float("inf")
+    g[15, d - 1] = -float("inf")
+    g[18] = 0.0
+    g[18, 5] = 3.4e38
+    rgc, _ = oracle.decode_bwd(d, m, idx, g.double().numpy())
+    got, _ = dpb.decode_bwd(plan, di, g.to(DEV))
+    got = got.cpu().numpy()
+    parents = slice(sum(K[:-2]), sum(K[:-1]))
+    for t in (12, 15):
+        assert np.array_equal(got[t, parents], rgc[t, parents].astype(np.float32))
+    compare_dense(got[18, parents][None], rgc[18, parents][None], TOL_F32)
+    rest = [t for t in range(T) if t not in (12, 15, 18)]
+    compare_dense(got[rest], rgc[rest], TOL_F32)
