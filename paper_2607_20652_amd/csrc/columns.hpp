@@ -338,10 +338,10 @@ __device__ __forceinline__ void col_tables(const ColPlan& C, const ColWave& W, c
 
 // Marks the basis slots' coordinates with slot + 1 and keeps their
 // coefficients by mark in W.bas (a coordinate held by several slots gathers
-// their coefficients in the marked one); lists the slots to be added one by
+// their coefficients, in slot order, in the marked one); lists the slots to be added one by
 // one and returns the largest number of them any token has, negative when
 // only their slot numbers are listed.  (Leaf slots that went into their
-// parent's column hold index -1 by now.)
+// parent's column hold a negative index by now.)
 template <int CPT>
 __device__ __forceinline__ int col_marks(const ColPlan& C, const ColWave& W, const float* cf)
 {
@@ -361,15 +361,20 @@ __device__ __forceinline__ int col_marks(const ColPlan& C, const ColWave& W, con
         unsigned char* m = W.mark + tt * C.mstride + c;
         float* bas = W.bas + tt * (k + 1) + 1;
         const float a = basis ? cf[i] : 0.f;
-        const bool mine = basis && *m == 0;   // not marked by an earlier block
-        if (mine) {
-            *m = (unsigned char)(s + 1);
+        const bool fresh = basis && *m == 0;   // not marked by an earlier block
+        if (fresh) {
+            *m = (unsigned char)(s + 1);   // of several slots any one
             bas[s] = a;
         }
         wave_sync();
-        if (basis) {
-            const int owner = (int)*m - 1;
-            if (owner != s) atomicAdd(&bas[owner], a);
+        const int owner = basis ? (int)*m - 1 : s;
+        if (__ballot(owner != s)) {
+            // a repeated coordinate: its slots are added in slot order
+            if (fresh && owner == s) bas[s] = 0.f;
+            for (uint64_t left = __ballot(basis); left; left &= left - 1) {
+                if (lane == __builtin_ctzll(left)) bas[owner] += a;
+                wave_sync();
+            }
         }
         wave_sync();
     }
@@ -644,8 +649,10 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
     wave_sync();
 }
 
-// Clears alpha, then adds each routed leaf coefficient to its cell (an index
-// listed twice gathers both) and takes the slot off the list (index -1).
+// Clears alpha, then adds each routed leaf coefficient to its cell and takes
+// the slot off the list (a negative index).  An index listed several times
+// gathers its slots in slot order: a cell that already held something sends
+// the group through the adds again, one slot after another.
 // route(tt, s) gives the route of a leaf slot.
 template <int CPT, typename Route>
 __device__ __forceinline__ void col_alpha(const ColPlan& C, const ColWave& W, const float* cf, Route route)
@@ -653,14 +660,36 @@ __device__ __forceinline__ void col_alpha(const ColPlan& C, const ColWave& W, co
     if constexpr (CPT == 0) return;
     constexpr int TPW = col_tpw(CPT);
     float* alpha = (float*)W.tab;
+    const int n = TPW * C.KL;
+    auto slot = [&](int i) {
+        const int tt = item_token<TPW>(i, C.KL);
+        return tt * C.k + C.sbL + i - tt * C.KL;
+    };
     *(float4*)(alpha + 4 * W.lane) = make_float4(0.f, 0.f, 0.f, 0.f);
     wave_sync();
-    for (int i = W.lane; i < TPW * C.KL; i += 64) {
-        const int tt = item_token<TPW>(i, C.KL), s = C.sbL + i - tt * C.KL;
-        const int rt = route(tt, s);
+    bool again = false;
+    for (int i = W.lane; i < n; i += 64) {
+        const int tt = item_token<TPW>(i, C.KL), at = slot(i);
+        const int rt = route(tt, at - tt * C.k);
         if (rt >= 0) {
-            atomicAdd(&alpha[(tt * CPT + (rt >> 16)) * 16 + (rt & 0xFFFF)], cf[tt * C.k + s]);
-            W.idx[tt * C.k + s] = -1;
+            const int cell = (tt * CPT + (rt >> 16)) * 16 + (rt & 0xFFFF);
+            again |= atomicAdd(&alpha[cell], cf[at]) != 0.f;
+            W.idx[at] = -2 - cell;
+        } else {
+            W.idx[at] = max(W.idx[at], -1);
+        }
+    }
+    if (__ballot(again)) {
+        wave_sync();
+        *(float4*)(alpha + 4 * W.lane) = make_float4(0.f, 0.f, 0.f, 0.f);
+        wave_sync();
+        for (int i0 = 0; i0 < n; i0 += 64) {
+            const int i = i0 + W.lane, at = slot(min(i, n - 1));
+            const int cell = i < n ? -2 - W.idx[at] : -1;
+            for (uint64_t left = __ballot(cell >= 0); left; left &= left - 1) {
+                if (W.lane == __builtin_ctzll(left)) alpha[cell] += cf[at];
+                wave_sync();
+            }
         }
     }
     wave_sync();

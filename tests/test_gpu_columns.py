@@ -148,3 +148,38 @@ def test_infinite_fp32_gradient_reaches_the_parents_signed(name):
     compare_dense(got[18, parents][None], rgc[18, parents][None], TOL_F32)
     rest = [t for t in range(T) if t not in (12, 15, 18)]
     compare_dense(got[rest], rgc[rest], TOL_F32)
+
+
+@pytest.mark.parametrize("name", ["cpt8", "cpt4_d200", "cpt16", "odd_d", "table_2l", "one_level"])
+def test_repeated_slots_add_in_slot_order(name):
+    """A coordinate, or a leaf, that several slots hold gets the fp32 sum of
+    their coefficients in slot order: the values are chosen so that every other
+    order gives another sum."""
+    d, nb, K = PLANS[name][:3]
+    L, base = len(nb), np.concatenate([[0], np.cumsum(K)]).astype(int)
+    plan = dpb.Plan(d, seed=0, level_bits=list(nb), branchings=[0] + [branch(name)] * (L - 1), active=list(K))
+    print(f"[repeated slots] {name}", flush=True)
+    orders = [(1e8, 1.0, -1e8), (1e8, -1e8, 1.0), (1.0, 1e8, -1e8), (-1e8, 1e8, 1.0), (1.0, -1e8, 1e8), (-1e8, 1.0, 1e8)]
+    idx = np.full((2 * len(orders), sum(K)), -1, np.int32)
+    coef = np.zeros(idx.shape, np.float32)
+    want = np.zeros((idx.shape[0], d), np.float32)
+    leaf_gens = oracle.generators(list(nb), [0] + [branch(name)] * (L - 1), 0)[L - 1] if L > 1 else None
+    m = oracle.masks(d, nb[-1])
+    columns = L > 1 and len(PLANS[name]) == 3
+    for t in range(idx.shape[0]):
+        val = orders[t % len(orders)]
+        total = np.float32(np.float32(np.float32(val[0]) + np.float32(val[1])) + np.float32(val[2]))
+        if t < len(orders):   # a basis coordinate in three slots, the last two as far apart as the code is wide
+            at = [0, 1, sum(K) - 1]
+            idx[t, at], coef[t, at] = d - 1, val
+            want[t, d - 1] = total
+        elif columns:         # a child of the last parent slot in three leaf slots
+            p = 5 % d
+            idx[t, base[L - 1] - 1] = p
+            at = [base[L - 1], base[L - 1] + 2, sum(K) - 1]
+            c = int(p) ^ int(leaf_gens[3])
+            idx[t, at], coef[t, at] = c, val
+            want[t] = oracle.decode(d, m, np.array([[c]], np.int32), np.array([[float(total)]]))[0].astype(np.float32)
+    y = dpb.decode(plan, torch.from_numpy(idx).to(DEV), torch.from_numpy(coef).to(DEV), torch.float32).cpu().numpy()
+    assert np.array_equal(y == 0, want == 0)
+    compare_dense(y, want, TOL_F32)
