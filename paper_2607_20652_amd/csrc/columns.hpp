@@ -36,7 +36,8 @@
 // Basis slots mark their coordinate in a byte map; the lane that owns a marked
 // coordinate adds the slot's coefficient before it writes.  Hashed slots
 // that fit nowhere else (a leaf that routes to no parent, a hashed index in a
-// level-0 slot: codes the encoder does not produce) are added one by one.
+// level-0 slot: codes the encoder does not produce) are added one by one up
+// to sixteen a token, through the tables beyond (col_pass).
 #pragma once
 
 #include <algorithm>
@@ -285,10 +286,12 @@ __device__ __forceinline__ ColFrag col_frag(const float* alpha, int lane)
 // Tables of each word of 32 listed indices: sign words (row v of group g =
 // bits parity(x_b & (v << 4g))) and signed sums of four coefficients (row v
 // of group i, times 1/sqrt d).  Two words (32 lanes each) per round.
-template <int CPT, int NG>
-__device__ __forceinline__ void col_tables(const ColPlan& C, const ColWave& W, const float* cf)
+// slot(tt, w, b, sum) gives the code slot of bit b of word w of token tt (-1:
+// none) and whether its coefficient is summed here.
+template <int CPT, int NG, typename Slot>
+__device__ __forceinline__ void col_tables(const ColPlan& C, const ColWave& W, const float* cf, Slot slot)
 {
-    constexpr int TPW = col_tpw(CPT), PN = col_parent_nibbles(CPT);
+    constexpr int TPW = col_tpw(CPT);
     const int lane = W.lane, b = lane & 31, v = lane & 15;
     const uint32_t x0 = -(uint32_t)(v & 1), x1 = -(uint32_t)((v >> 1) & 1), x2 = -(uint32_t)((v >> 2) & 1),
                    x3 = -(uint32_t)((v >> 3) & 1);
@@ -297,18 +300,8 @@ __device__ __forceinline__ void col_tables(const ColPlan& C, const ColWave& W, c
         const int unit = min(u0 + (lane >> 5), units - 1);
         const int tt = TPW == 1 ? 0 : item_token<TPW>(unit, C.words);
         const int w = unit - tt * C.words;
-        // listed slot of bit b: a parent in the low bits of the half-words of word 0, else a summed slot
-        const int hb = b & 15, hi = b >> 4;
-        int i = 32 * w + b - 32 + col_word0_slots(CPT);   // summed slot of words 1 ..
-        int s = -1;
         bool sum = true;
-        if (w == 0) {
-            i = (16 - 4 * PN) * hi + hb - 4 * PN;
-            sum = hb >= 4 * PN;
-            const int q = 2 * hb + hi;
-            if (hb < CPT / 2 && q < C.KP) s = C.sbP + q;
-        }
-        if (sum) s = i < C.ns ? C.ss + i : -1;
+        const int s = slot(tt, w, b, sum);
         const int at = tt * C.k + max(s, 0);
         const int32_t c = s >= 0 ? W.idx[at] : 0;
         W.scr[64 + lane] = __float_as_uint(sum && s >= 0 && c >= C.d ? cf[at] : 0.f);
@@ -336,12 +329,61 @@ __device__ __forceinline__ void col_tables(const ColPlan& C, const ColWave& W, c
     }
 }
 
+// The tables of the plan's own list: a parent in the low bits of the
+// half-words of word 0, else a summed slot.
+template <int CPT, int NG>
+__device__ __forceinline__ void col_list_tables(const ColPlan& C, const ColWave& W, const float* cf)
+{
+    constexpr int PN = col_parent_nibbles(CPT);
+    col_tables<CPT, NG>(C, W, cf, [&](int, int w, int b, bool& sum) {
+        const int hb = b & 15, hi = b >> 4;
+        int i = 32 * w + b - 32 + col_word0_slots(CPT);   // summed slot of words 1 ..
+        if (w == 0) {
+            i = (16 - 4 * PN) * hi + hb - 4 * PN;
+            sum = hb >= 4 * PN;
+            const int q = 2 * hb + hi;
+            if (!sum) return hb < CPT / 2 && q < C.KP ? C.sbP + q : -1;
+        }
+        return i < C.ns ? C.ss + i : -1;
+    });
+}
+
+// The sign word of a coordinate (its row mask's even and odd nibbles as table
+// offsets) from the tables at vb.
+template <int NG>
+__device__ __forceinline__ uint32_t col_word(uint32_t vb, uint32_t even, uint32_t odd)
+{
+    uint32_t r[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+        r[g] = lds_ld(__builtin_amdgcn_perm(vb, (g & 1) ? odd : even, 0x07060500u | (uint32_t)(g >> 1)) +
+                      (uint32_t)(g * 64));
+    uint32_t x = xor3(r[0], r[1], r[2]);
+    if constexpr (NG == 4) x ^= r[3];
+    if constexpr (NG >= 5) x = xor3(x, r[3], r[4]);
+    if constexpr (NG == 6) x ^= r[5];
+    if constexpr (NG == 8) x = xor3(x, r[5], r[6]) ^ r[7];
+    return x;
+}
+
+// t plus the signed coefficients of a whole word of slots, eight groups of
+// four from the sums at tb, with the signs of word x.
+__device__ __forceinline__ float col_word_sum(uint32_t tb, uint32_t x, float t)
+{
+    const uint32_t e4 = (x << 2) & 0x3C3C3C3Cu, o4 = (x >> 2) & 0x3C3C3C3Cu;
+#pragma unroll
+    for (int n = 0; n < 8; ++n)
+        t += lds_ldf(__builtin_amdgcn_perm(tb, (n & 1) ? o4 : e4, 0x07060500u | (uint32_t)(n >> 1)) +
+                     (uint32_t)(n * 64));
+    return t;
+}
+
 // Marks the basis slots' coordinates with slot + 1 and keeps their
 // coefficients by mark in W.bas (a coordinate held by several slots gathers
-// their coefficients, in slot order, in the marked one); lists the slots to be added one by
-// one and returns the largest number of them any token has, negative when
-// only their slot numbers are listed.  (Leaf slots that went into their
-// parent's column hold a negative index by now.)
+// their coefficients, in slot order, in the marked one); lists the slots that
+// fit nowhere else in W.xs and returns the largest number of them any token
+// has.  (Leaf slots that went into their parent's column hold a negative index
+// by now.)
 template <int CPT>
 __device__ __forceinline__ int col_marks(const ColPlan& C, const ColWave& W, const float* cf)
 {
@@ -393,26 +435,76 @@ __device__ __forceinline__ int col_marks(const ColPlan& C, const ColWave& W, con
         most = max(most, n);
     }
     wave_sync();
-    constexpr int cap = 64 / TPW;
-    if (most > cap) return -most;
-    // few (an edited code has a handful): index and scaled coefficient of
-    // each, zero past the last, where the tables' scratch is free by now
-    {
-        const int i = lane & (cap - 1), tt = lane / cap, s = i < most ? W.xs[tt * k + i] : 0xFFFF;
-        const int at = tt * k + (s == 0xFFFF ? 0 : s);
-        const float a = s == 0xFFFF ? 0.f : C.rsd * cf[at];
-        ((u32x2*)W.scr)[lane] = u32x2{(uint32_t)W.idx[at], __float_as_uint(a)};
-    }
-    wave_sync();
     return most;
+}
+
+// Unlisted slots of a token up to which they are added one by one: about ten
+// vector instructions a slot and step, against a table set-up per pass and
+// one instruction a slot.  Decode of 16,381 tokens d 768 k 96, us, one by one
+// and in passes: 8 slots 55 and 69, 16 slots 67 and 68, 32 slots 84 and 65; at
+// d 4096 k 80 (two waves a CU, where the set-ups' latency shows) 32 slots 685
+// and 785.  Without leaf columns all of them are added one by one: they are
+// hashed indices on level 0 alone.
+constexpr int col_few(int cpt) { return cpt ? 16 : 1 << 30; }
+
+// Index and scaled coefficient of the 64 / TPW slots of W.xs from number i0
+// on, zero past the last, where the tables' scratch is free by now.
+template <int CPT>
+__device__ __forceinline__ void col_stage_few(const ColPlan& C, const ColWave& W, const float* cf, int i0)
+{
+    constexpr int cap = 64 / col_tpw(CPT);
+    const int lane = W.lane, i = i0 + (lane & (cap - 1)), tt = lane / cap, s = i < C.k ? W.xs[tt * C.k + i] : 0xFFFF;
+    const int at = tt * C.k + (s == 0xFFFF ? 0 : s);
+    const float a = s == 0xFFFF ? 0.f : C.rsd * cf[at];
+    ((u32x2*)W.scr)[lane] = u32x2{(uint32_t)W.idx[at], __float_as_uint(a)};
+    wave_sync();
+}
+
+// Coordinate steps of a pass (twice the steps take twice the registers of sums:
+// four tokens a wave have them).
+constexpr int col_pass_steps(int cpt) { return cpt == 4 ? 8 : 4; }
+
+// Sums of the slots of W.xs (at most n per token) over the steps from m0 on,
+// as many words of them at a time as the plan's tables have room for.  The
+// tables are built anew for each pass, the plan's own after them: room for
+// both would take a workgroup a CU from every code.  A code of 64 leaves and
+// no parent, 16,381 tokens d 768, us: decode 254 one by one, 80 here (108 in
+// the row-in-LDS kernels); backward 344, 143 (174).
+template <int CPT, int NG>
+__device__ __forceinline__ void col_pass(const ColPlan& C, const ColWave& W, const float* cf, int n, int m0,
+                                         float (&ex)[2 * col_pass_steps(CPT)])
+{
+    constexpr int LPT = 64 / col_tpw(CPT), PS = col_pass_steps(CPT);
+    const uint32_t vb = lds_addr(W.tab) + (uint32_t)(W.lane / LPT * C.words) * 1024u;
+    const u32x4* mk = W.mask + (W.lane & (LPT - 1));
+#pragma unroll
+    for (int u = 0; u < 2 * PS; ++u) ex[u] = 0.f;
+    for (int i0 = 0; i0 < n; i0 += 32 * C.words) {
+        col_tables<CPT, NG>(C, W, cf, [&](int tt, int w, int b, bool&) {
+            const int i = i0 + 32 * w + b, s = i < C.k ? W.xs[tt * C.k + i] : 0xFFFF;
+            return s == 0xFFFF ? -1 : s;
+        });
+        for (int w = 0; w < min(C.words, (n - i0 + 31) / 32); ++w) {
+#pragma unroll
+            for (int u = 0; u < PS; ++u) {
+                const u32x4 sm = mk[min(m0 + u, C.steps - 1) * LPT];
+                const uint32_t v = vb + (uint32_t)w * 1024u;
+                ex[2 * u] = col_word_sum(v + 512u, col_word<NG>(v, sm.x, sm.y), ex[2 * u]);
+                ex[2 * u + 1] = col_word_sum(v + 512u, col_word<NG>(v, sm.z, sm.w), ex[2 * u + 1]);
+            }
+        }
+        wave_sync();
+    }
 }
 
 // The coordinate steps: G0 four-slot groups of word 0 are summed.  out (and
 // the optional add, which may alias it) are the rows of the wave's tokens,
-// row stride d.
-template <int CPT, int NG, bool OUT_BF16, int G0>
+// row stride d.  nx staged slots are added one by one; with PASS only the steps
+// of a pass from m0 on are taken, on top of its sums ex.
+template <int CPT, int NG, bool OUT_BF16, int G0, bool PASS = false>
 __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, const float* cf, const ColFrag& F,
-                                          f32x4 c0, int nx, int64_t row0, void* out, const void* add)
+                                          f32x4 c0, int nx, int64_t row0, void* out, const void* add, int m0 = 0,
+                                          float* ex = nullptr)
 {
     constexpr int TPW = col_tpw(CPT), LPT = 64 / TPW, NP = LPT / 16;   // NP 16-column blocks per pair half
     constexpr int PN = col_parent_nibbles(CPT);
@@ -441,8 +533,9 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
     const bool even = (C.d & 1) == 0;
     const float* bas = W.bas + tt * (C.k + 1);
     u32x4 B[NP];
-    fetch(0, B);
-    for (int m = 0; m < C.steps; ++m) {
+    const int mend = PASS ? min(m0 + col_pass_steps(CPT), C.steps) : C.steps;
+    fetch(PASS ? m0 : 0, B);
+    for (int m = PASS ? m0 : 0; m < mend; ++m) {
         const u32x4 sm = mk[m * LPT];
         const uint32_t mw = *(const uint16_t*)(mark + m * 2 * LPT);
         const float b0 = bas[mw & 255u], b1 = bas[mw >> 8];   // basis coefficients (mark 0: none)
@@ -466,21 +559,14 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
         // sign words and coefficient sums of the two coordinates
         uint32_t U[2];
         float t[2] = {b0, b1};
-        auto word = [&](uint32_t vbw, int e) {
-            uint32_t r[NG];
+        if constexpr (PASS) {
+            t[0] += ex[0];
+            t[1] += ex[1];
 #pragma unroll
-            for (int g = 0; g < NG; ++g)
-                r[g] = lds_ld(__builtin_amdgcn_perm(vbw, (g & 1) ? s1[e] : s0[e], 0x07060500u | (uint32_t)(g >> 1)) +
-                              (uint32_t)(g * 64));
-            uint32_t x = xor3(r[0], r[1], r[2]);
-            if constexpr (NG == 4) x ^= r[3];
-            if constexpr (NG >= 5) x = xor3(x, r[3], r[4]);
-            if constexpr (NG == 6) x ^= r[5];
-            if constexpr (NG == 8) x = xor3(x, r[5], r[6]) ^ r[7];
-            return x;
-        };
+            for (int u = 0; u + 2 < 2 * col_pass_steps(CPT); ++u) ex[u] = ex[u + 2];
+        }
 #pragma unroll
-        for (int e = 0; e < 2; ++e) U[e] = word(vb, e);
+        for (int e = 0; e < 2; ++e) U[e] = col_word<NG>(vb, s0[e], s1[e]);
         if constexpr (G0 > 0) {
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
@@ -494,16 +580,9 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
             }
         }
         for (int w = 1; w < C.words; ++w) {
+            const uint32_t v = vb + (uint32_t)w * 1024u;
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const uint32_t x = word(vb + (uint32_t)w * 1024u, e);
-                const uint32_t e4 = (x << 2) & 0x3C3C3C3Cu, o4 = (x >> 2) & 0x3C3C3C3Cu;
-#pragma unroll
-                for (int n = 0; n < 8; ++n)
-                    t[e] += lds_ldf(__builtin_amdgcn_perm(tb + (uint32_t)w * 1024u, (n & 1) ? o4 : e4,
-                                                          0x07060500u | (uint32_t)(n >> 1)) +
-                                    (uint32_t)(n * 64));
-            }
+            for (int e = 0; e < 2; ++e) t[e] = col_word_sum(v + 512u, col_word<NG>(v, s0[e], s1[e]), t[e]);
         }
         // the parents' signs on this lane's four columns, then the token's columns summed
         float y[2];
@@ -563,7 +642,7 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
             }
             y[e] = __builtin_fmaf(C.rsd, leaf, t[e]);
         }
-        if (nx) {
+        if (!PASS && nx) {
             // slots added one by one: sign = parity of the row mask and the index
             const uint32_t M0 = (s0[0] >> 2) | (s1[0] << 2), M1 = (s0[1] >> 2) | (s1[1] << 2);
             auto add_slot = [&](uint32_t c, float a) {
@@ -571,16 +650,20 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
                 y[1] += signed_by_parity(a, M1 & c);
             };
             const u32x2* few = (const u32x2*)W.scr + tt * (64 / TPW);
-            for (int i = 0; i < nx; i += 4) {
-                u32x2 q[4];
+            constexpr int cap = 64 / TPW;
+            for (int i0 = 0; i0 < nx; i0 += cap) {
+                if (CPT == 0 && nx > cap) {   // more than the scratch holds
+                    wave_sync();
+                    col_stage_few<CPT>(C, W, cf, i0);
+                }
+                for (int i = 0; i < min(nx - i0, cap); i += 4) {
+                    u32x2 q[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) q[u] = few[i + u];
+                    for (int u = 0; u < 4; ++u) q[u] = few[i + u];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) add_slot(q[u].x, __uint_as_float(q[u].y));
-            }
-            for (int i = 0; i < -nx; ++i) {
-                const int s = W.xs[tt * C.k + i], at = tt * C.k + (s == 0xFFFF ? 0 : s);
-                add_slot((uint32_t)W.idx[at], s == 0xFFFF ? 0.f : C.rsd * cf[at]);
+                    for (int u = 0; u < 4; ++u) add_slot(q[u].x, __uint_as_float(q[u].y));
+                }
+                if (CPT > 0) break;   // col_few of them at most
             }
         }
         if (m * 2 * LPT < lim) {
@@ -636,11 +719,28 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
         c0 = *(const f32x4*)(W.pc + 4 * (lane >> 4));
         wave_sync();
     }
-    col_tables<CPT, NG>(C, W, cf);
+    constexpr int MG = col_word0_slots(CPT) / 4;   // groups of word 0
     const int nx = col_marks<CPT>(C, W, cf);
+    if (CPT > 0 && nx > col_few(CPT)) {
+        // the tables hold the unlisted slots of a few steps and the listed ones
+        // of the same steps in turn
+        ColWave V = W;
+        for (int m0 = 0; m0 < C.steps; m0 += col_pass_steps(CPT)) {
+            float ex[2 * col_pass_steps(CPT)];
+            __asm__ volatile("" : "+v"(V.lane));   // nothing of this path is worked out before it
+            col_pass<CPT, NG>(C, V, cf, nx, m0, ex);
+            __asm__ volatile("" : "+v"(V.lane));
+            col_list_tables<CPT, NG>(C, V, cf);
+            __asm__ volatile("" : "+v"(V.lane));
+            col_steps<CPT, NG, OUT_BF16, MG, true>(C, V, cf, F, c0, 0, row0, out, add, m0, ex);
+            wave_sync();
+        }
+        return;
+    }
+    col_list_tables<CPT, NG>(C, W, cf);
+    if (nx) col_stage_few<CPT>(C, W, cf, 0);
     wave_sync();
     const int g0 = min(C.ns, col_word0_slots(CPT));
-    constexpr int MG = col_word0_slots(CPT) / 4;   // groups of word 0
     if (g0 == 0) col_steps<CPT, NG, OUT_BF16, 0>(C, W, cf, F, c0, nx, row0, out, add);
     else if (g0 <= 8) col_steps<CPT, NG, OUT_BF16, 2>(C, W, cf, F, c0, nx, row0, out, add);
     else if (MG == 4 || g0 <= 16) col_steps<CPT, NG, OUT_BF16, 4>(C, W, cf, F, c0, nx, row0, out, add);
@@ -649,46 +749,69 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
     wave_sync();
 }
 
-// Clears alpha, then adds each routed leaf coefficient to its cell and takes
-// the slot off the list (a negative index).  An index listed several times
-// gathers its slots in slot order: a cell that already held something sends
-// the group through the adds again, one slot after another.
+// Clears alpha (to -0: a cell that still reads -0 holds nothing, and -0 adds
+// nothing), then adds each routed leaf coefficient to its cell and takes the
+// slot off the list (a negative index).  An index listed several times
+// gathers its slots in slot order: two slots give the same sum in either
+// order, and a cell that three or more go to sends the group through the adds
+// again, one slot after another.
 // route(tt, s) gives the route of a leaf slot.
 template <int CPT, typename Route>
 __device__ __forceinline__ void col_alpha(const ColPlan& C, const ColWave& W, const float* cf, Route route)
 {
     if constexpr (CPT == 0) return;
     constexpr int TPW = col_tpw(CPT);
+    static_assert(TPW * kColMaxSlots <= 64 * 32, "a bit per round of 64 leaf slots");
     float* alpha = (float*)W.tab;
     const int n = TPW * C.KL;
     auto slot = [&](int i) {
         const int tt = item_token<TPW>(i, C.KL);
         return tt * C.k + C.sbL + i - tt * C.KL;
     };
-    *(float4*)(alpha + 4 * W.lane) = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto taken = [](float old) { return (uint32_t)(__float_as_uint(old) != 0x80000000u); };
+    float none = -0.f;
+    __asm__ volatile("" : "+v"(none));   // four registers of it would be kept across the groups
+    *(float4*)(alpha + 4 * W.lane) = make_float4(none, none, none, none);
     wave_sync();
-    bool again = false;
+    uint32_t again = 0, bit = 1;   // a bit per round: this lane's cell already held something
+    float old = -0.f;              // looked at a round later, when it has arrived
     for (int i = W.lane; i < n; i += 64) {
         const int tt = item_token<TPW>(i, C.KL), at = slot(i);
         const int rt = route(tt, at - tt * C.k);
+        again |= taken(old) * (bit >> 1);
+        old = -0.f;
         if (rt >= 0) {
             const int cell = (tt * CPT + (rt >> 16)) * 16 + (rt & 0xFFFF);
-            again |= atomicAdd(&alpha[cell], cf[at]) != 0.f;
+            old = atomicAdd(&alpha[cell], cf[at]);
             W.idx[at] = -2 - cell;
         } else {
             W.idx[at] = max(W.idx[at], -1);
         }
+        bit <<= 1;
     }
-    if (__ballot(again)) {
+    again |= taken(old) * (bit >> 1);
+    if (__ballot(again != 0)) {
+        int lane = W.lane;
+        __asm__ volatile("" : "+v"(lane));   // nothing of this path is worked out before it
+        if (lane < 8) W.scr[lane] = 0;
         wave_sync();
-        *(float4*)(alpha + 4 * W.lane) = make_float4(0.f, 0.f, 0.f, 0.f);
-        wave_sync();
-        for (int i0 = 0; i0 < n; i0 += 64) {
-            const int i = i0 + W.lane, at = slot(min(i, n - 1));
-            const int cell = i < n ? -2 - W.idx[at] : -1;
-            for (uint64_t left = __ballot(cell >= 0); left; left &= left - 1) {
-                if (W.lane == __builtin_ctzll(left)) alpha[cell] += cf[at];
-                wave_sync();
+        bool third = false;
+        for (int i = lane; again; i += 64, again >>= 1)
+            if (again & 1u) {
+                const int cell = -2 - W.idx[slot(i)];
+                third |= ((atomicOr(&W.scr[cell >> 5], 1u << (cell & 31)) >> (cell & 31)) & 1u) != 0;
+            }
+        if (__ballot(third)) {
+            wave_sync();
+            *(float4*)(alpha + 4 * lane) = make_float4(0.f, 0.f, 0.f, 0.f);
+            wave_sync();
+            for (int i0 = 0; i0 < n; i0 += 64) {
+                const int i = i0 + lane, at = slot(min(i, n - 1));
+                const int cell = i < n ? -2 - W.idx[at] : -1;
+                for (uint64_t left = __ballot(cell >= 0); left; left &= left - 1) {
+                    if (lane == __builtin_ctzll(left)) alpha[cell] += cf[at];
+                    wave_sync();
+                }
             }
         }
     }

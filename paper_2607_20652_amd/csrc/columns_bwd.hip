@@ -80,16 +80,18 @@ __device__ __forceinline__ void col_scores(const ColPlan& C, const DevPlan& P, c
     if constexpr (CPT > 0) {   // the leaf parents: column tt CPT + q
         const int tt = col / CPT, q = col & (CPT - 1);
         const int32_t p = q < C.KP ? S.idx[tt * k + C.sbP + q] : -1;
-        index_bitmaps(P, lane, p, P.nt, S.cw);
-        wave_sync();
-        column_products<G_BF16, true>(P, S, tt, s, o);
+        if (!G_BF16 || __ballot(p >= 0)) {   // no parent: no leaf has a route (fp32 measured slower with the branch)
+            index_bitmaps(P, lane, p, P.nt, S.cw);
+            wave_sync();
+            column_products<G_BF16, true>(P, S, tt, s, o);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) S.score[col * 16 + kq * 4 + i] = s[i] * C.rsd;
-        if (kq == 0 && p >= C.d) S.coef[tt * k + C.sbP + q] = o[0] * C.rsd;
-        wave_sync();
-        for (int i = lane; i < TPW * C.KL; i += 64) {
-            const int t2 = item_token<TPW>(i, C.KL), at = t2 * k + C.sbL + i - t2 * C.KL, rt = S.route[at];
-            if (rt >= 0) S.coef[at] = S.score[(t2 * CPT + (rt >> 16)) * 16 + (rt & 0xFFFF)];
+            for (int i = 0; i < 4; ++i) S.score[col * 16 + kq * 4 + i] = s[i] * C.rsd;
+            if (kq == 0 && p >= C.d) S.coef[tt * k + C.sbP + q] = o[0] * C.rsd;
+            wave_sync();
+            for (int i = lane; i < TPW * C.KL; i += 64) {
+                const int t2 = item_token<TPW>(i, C.KL), at = t2 * k + C.sbL + i - t2 * C.KL, rt = S.route[at];
+                if (rt >= 0) S.coef[at] = S.score[(t2 * CPT + (rt >> 16)) * 16 + (rt & 0xFFFF)];
+            }
         }
     }
     if constexpr (G_BF16) {
@@ -97,6 +99,7 @@ __device__ __forceinline__ void col_scores(const ColPlan& C, const DevPlan& P, c
             const int i = i0 + col, tt = min(item_token<TPW>(i, C.ns), TPW - 1);
             const int at = tt * k + C.ss + i - tt * C.ns;
             const int32_t c = i < TPW * C.ns ? S.idx[at] : -1;
+            if (!__ballot(c >= C.d)) continue;   // basis slots and padding
             wave_sync();
             index_bitmaps(P, lane, c, P.nt, S.cw);
             wave_sync();

@@ -42,6 +42,7 @@ PLANS = {
     "table_odd": (333, (9, 13, 17), (16, 16, 16), 16),       # 32 slots: one full word
     "table_254": (512, (9, 13, 17), (16, 110, 128), 64),     # the widest code of marks
     "one_level": (300, (9,), (20,), 16),
+    "table_k0": (300, (9, 13), (100, 64), 64),               # up to 100 hashed indices on level 0
 }
 
 
@@ -183,3 +184,68 @@ def test_repeated_slots_add_in_slot_order(name):
     y = dpb.decode(plan, torch.from_numpy(idx).to(DEV), torch.from_numpy(coef).to(DEV), torch.float32).cpu().numpy()
     assert np.array_equal(y == 0, want == 0)
     compare_dense(y, want, TOL_F32)
+
+
+@pytest.mark.parametrize("name", ["cpt8", "cpt4_d200", "cpt16", "odd_d", "basis_parents", "one_step", "many_words",
+                                  "table_2l", "table_k0"])
+def test_unlisted_slots(name):
+    """Any number of slots that fit neither a parent's column nor the plan's own
+    tables (leaves without a listed parent, hashed indices on level 0), from one
+    to all of them, next to tokens of the same wave that have none: at, below
+    and above the count up to which they are added one by one."""
+    d, nb, K = PLANS[name][:3]
+    L, k, N = len(nb), sum(K), 1 << nb[-1]
+    base = np.concatenate([[0], np.cumsum(K)]).astype(int)
+    print(f"[unlisted] {name}", flush=True)
+    plan = dpb.Plan(d, seed=0, level_bits=list(nb), branchings=[0] + [branch(name)] * (L - 1), active=list(K))
+    m = oracle.masks(d, nb[-1])
+    counts = [0, 1, 4, 15, 16, 17, 31, 32, 33, 63, 64, 65, k]
+    idx, _ = codes(name, 4 * len(counts), 9500 + d)
+    idx, rng = idx[-4 * len(counts):], np.random.default_rng(9600 + d)
+    open_slots = np.r_[base[L - 1]:k, 0:(K[0] if L != 2 or len(PLANS[name]) > 3 else 0)]   # leaves, then level 0
+    for t in range(idx.shape[0]):
+        n = min(counts[t // 4], len(open_slots)) if t % 4 != 2 else 0
+        idx[t, open_slots[:n]] = rng.integers(d, N, n)
+        if t % 4 == 3:
+            idx[t, (base[L - 2] if L > 1 else 0):base[L - 1]] = -1   # no parents: a code of leaves alone
+    coef = rng.standard_normal(idx.shape).astype(np.float32)
+    coef[idx < 0] = 0.0
+    di, dc = torch.from_numpy(idx).to(DEV), torch.from_numpy(coef).to(DEV)
+    ref = oracle.decode(d, m, idx, coef.astype(np.float64))
+    for dt, tol in ((torch.float32, TOL_F32), (torch.bfloat16, TOL_BF16)):
+        compare_dense(dpb.decode(plan, di, dc, dt).float().cpu().numpy(), ref, tol)
+        g = inputs.normal(idx.shape[:1] + (d,), 9700 + d, "f32").to(dt)
+        rgc, rgx = oracle.decode_bwd(d, m, idx, g.double().numpy())
+        gc, gx = dpb.decode_bwd(plan, di, g.to(DEV), gx_dtype=torch.float32)
+        compare_dense(gc.cpu().numpy(), rgc, TOL_F32)
+        compare_dense(gx.cpu().numpy(), rgx, TOL_F32)
+
+
+def _call_us(fn, reps=9, inner=4):
+    for _ in range(3):
+        fn()
+    ev = [[torch.cuda.Event(enable_timing=True) for _ in range(2)] for _ in range(reps)]
+    for a, b in ev:
+        a.record()
+        for _ in range(inner):
+            fn()
+        b.record()
+    torch.cuda.synchronize()
+    return sorted(a.elapsed_time(b) * 1000 / inner for a, b in ev)[reps // 2]
+
+
+def test_codes_of_unlisted_leaves_keep_the_table_rate():
+    """A code of leaves alone (parents taken off) decodes through tables as a
+    whole code does: at 16,384 tokens of d 768, k 96 it takes 1.9 to 2.0 times
+    the whole code's time.  Added one by one the 64 leaves took 6.4 times."""
+    d, nb, K = PLANS["cpt8"][:3]
+    plan = dpb.Plan(d, seed=0, level_bits=list(nb), branchings=[0] + [16] * (len(nb) - 1), active=list(K))
+    x = inputs.normal((16384, d), 9800, "bf16").to(DEV)
+    idx, coef = dpb.encode(plan, x)
+    leaves, lc = idx.clone(), coef.clone()
+    leaves[:, : sum(K[:-1])] = -1
+    lc[:, : sum(K[:-1])] = 0
+    whole = _call_us(lambda: dpb.decode(plan, idx, coef, torch.bfloat16))
+    alone = _call_us(lambda: dpb.decode(plan, leaves, lc, torch.bfloat16))
+    print(f"[leaf-only decode] whole {whole:.1f} us, leaves alone {alone:.1f} us", flush=True)
+    assert alone < 3.5 * whole
