@@ -49,16 +49,24 @@ __device__ __forceinline__ float signed_by_parity(float a, uint32_t m)
 }
 
 // AbsTopK key: |s| (fp32 bits) first, then the smaller index; the sign of s
-// rides in bit 0 so that the signed coefficient can be rebuilt.  A NaN's
-// payload is bounded so that a key's bits, read as a double, are never
-// infinite or NaN: key_max and key_min compare keys as positive doubles.
+// rides in bit 0 so that the signed coefficient can be rebuilt.
 __device__ __forceinline__ uint64_t make_key(float s, uint32_t idx)
+{
+    const uint32_t u = __float_as_uint(s);
+    return ((uint64_t)(u & 0x7FFFFFFFu) << 32) | (uint64_t)(((0x7FFFFFFFu - idx) << 1) | (u >> 31));
+}
+
+// The same for keys that key_max and key_min compare as positive doubles: a
+// NaN's payload is bounded so that a key's bits, read as a double, are never
+// infinite or NaN.  (One instruction more: where keys are compared as whole
+// numbers, make_key serves.)
+__device__ __forceinline__ uint64_t make_sort_key(float s, uint32_t idx)
 {
     const uint32_t u = __float_as_uint(s);
     return ((uint64_t)min(u & 0x7FFFFFFFu, 0x7FEFFFFFu) << 32) | (uint64_t)(((0x7FFFFFFFu - idx) << 1) | (u >> 31));
 }
 
-// Larger and smaller of two keys, one instruction each: positive finite
+// Larger and smaller of two sort keys, one instruction each: positive finite
 // doubles order as their bits do, denormals included (the fp64 denormal mode
 // is on), and v_max_f64 runs at the full vector rate here (a 64-bit compare and
 // two selects take three).

@@ -552,7 +552,7 @@ __global__ __launch_bounds__(kEncThreads, (X_BF16 && (CPT == 16 || CPT == 8) && 
                     const uint32_t c = ok ? (uint32_t)p ^ gens[j] : 0u;
                     float sc = acc[i] * P.rsd;
                     if constexpr (STD) sc = (sc - stv[4 * mb + i].x) * stv[4 * mb + i].y;
-                    keys[4 * mb + i] = ok ? make_key(sc, c) : 0ull;
+                    keys[4 * mb + i] = ok ? make_sort_key(sc, c) : 0ull;
                 }
             }
             // Levels that keep few of their candidates (K_l <= 2 CPT, the beam
@@ -1306,7 +1306,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_select_kernel(DevPlan P, in
         const uint64_t* ent = (const uint64_t*)src;
         for (int e = lane; e < listed; e += 64) {
             const uint64_t en = ent[e];
-            lst[e] = make_key(__uint_as_float((uint32_t)en), child_index((int)(en >> 32)));
+            lst[e] = make_sort_key(__uint_as_float((uint32_t)en), child_index((int)(en >> 32)));
         }
         wave_sync();
         nl = listed;
@@ -1381,7 +1381,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_select_kernel(DevPlan P, in
                 mine[j] = 0ull;
                 if (j < mine_n) {
                     const uint64_t en = lst[lane * kSegStride + j];
-                    mine[j] = make_key(__uint_as_float((uint32_t)en), child_index((int)(en >> 32)));
+                    mine[j] = make_sort_key(__uint_as_float((uint32_t)en), child_index((int)(en >> 32)));
                 }
             }
             const int pre = wave_prefix5(mine_n, lane, nl);
@@ -1411,7 +1411,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_select_kernel(DevPlan P, in
                 for (int b = 0; b < B; ++b) {
                     const int f = (rd * B + b) * 64 + lane;
                     const bool ok = is_live(f);
-                    const uint64_t k = ok ? make_key(z_of(f, v[b]), child_index(f)) : 0ull;
+                    const uint64_t k = ok ? make_sort_key(z_of(f, v[b]), child_index(f)) : 0ull;
                     best = (k < last && k > best) ? k : best;
                 }
             }
