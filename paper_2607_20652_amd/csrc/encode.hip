@@ -91,13 +91,13 @@ __host__ __device__ inline unsigned enc_shared_bytes(const DevPlan& P, bool std)
     return align16u(P.nt_groups * 16 * P.nchunk * 4) + align16u(P.gens_total * 4) + (std ? align16u(P.d * 8) : 0u);
 }
 
-// The layout in use: where the LDS holds it, lists of two keys per lane (the
+// The layout in use: where the LDS holds it, lists of one key per lane (the
 // beam levels' selection).
 inline EncLayout enc_layout(const DevPlan& P, bool act_bf16, bool std)
 {
     const EncLayout least = enc_layout_least(P, act_bf16, std);
-    const int two = 2 * (64 / P.wave_tokens);
-    const EncLayout L = enc_layout_with(P, act_bf16, least.listn > two ? least.listn : two);
+    const int lanes = 64 / P.wave_tokens;
+    const EncLayout L = enc_layout_with(P, act_bf16, least.listn > lanes ? least.listn : lanes);
     return enc_shared_bytes(P, std) + kEncWaves * L.bytes <= (unsigned)kLdsBudget ? L : least;
 }
 
@@ -560,18 +560,19 @@ __global__ __launch_bounds__(kEncThreads, (X_BF16 && (CPT == 16 || CPT == 8) && 
             // least K_l keys reach it); the keys with a magnitude >= tau are
             // listed (at most one per lane of the token), each lane counts
             // the listed keys above its own, and the key goes to that place of
-            // a second list.  Equal keys (a child reached from two parents)
+            // the list.  Equal keys (a child reached from two parents)
             // share a place and leave the next one empty, so the distinct keys
-            // are the occupied places in order.  A token with more listed keys
-            // than lanes, or with fewer than K_l distinct ones although not
-            // all are listed, sorts all its keys.  (Sorting the list as 64-bit
-            // keys and ranking by ballots took 270 vector instructions a
+            // are the occupied places in order.  A token with fewer than K_l
+            // distinct ones although not all are listed takes the K_l-th
+            // distinct lane maximum for tau and lists again; one with more
+            // listed keys than lanes sorts all its keys.  (Sorting the list
+            // as 64-bit keys and ranking by ballots took 270 vector instructions a
             // level, this takes about 150; with the sort of fixed directions:
             // 65,536 tokens d 768 268 -> 238 us, 16,384 tokens d 1024 N 2^24
             // 188 -> 171, standardized 367 -> 331.)
             const int Kl = P.active[l];
             bool done = false;
-            if (Kl <= 2 * CPT && EL.listn >= 8 * CPT) {
+            if (Kl <= 2 * CPT && EL.listn >= 4 * CPT) {
                 uint32_t mg[R], top[1] = {0u};
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
@@ -579,37 +580,42 @@ __global__ __launch_bounds__(kEncThreads, (X_BF16 && (CPT == 16 || CPT == 8) && 
                     top[0] = max(top[0], mg[r]);
                 }
                 uint64_t* tl = list + ct * EL.listn;
-                uint64_t* placed = tl + 4 * CPT;
-                tl[lanepos] = 0ull;
-                placed[lanepos] = 0ull;
-                if (lanepos == 0) cnt[ct] = 0;
                 sort_desc<1, NB, true>(top, lanepos, x32);
                 // the lane at position K_l - 1 of my token
                 const int at = Kl - 1, src = ct * CPT + (at >> 2) + 16 * (at & 3);
-                const uint32_t tau = (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)top[0]);
-                uint32_t hits = 0u;
+                uint32_t tau = (uint32_t)__builtin_amdgcn_ds_bpermute(src << 2, (int)top[0]);
+                for (bool again = false;; again = true) {
+                    uint32_t z = 0;
+                    __asm__ volatile("" : "+v"(z));   // not kept in registers across the levels
+                    const uint64_t none = ((uint64_t)z << 32) | z;
+                    tl[lanepos] = none;
+                    if (lanepos == 0) cnt[ct] = 0;
+                    uint32_t hits = 0u;
 #pragma unroll
-                for (int r = 0; r < R; ++r) hits |= (uint32_t)(keys[r] != 0ull && mg[r] >= tau) << r;
-                wave_sync();
-                int pos = hits ? atomicAdd(&cnt[ct], (int)__popc(hits)) : 0;
+                    for (int r = 0; r < R; ++r) hits |= (uint32_t)(keys[r] != 0ull && mg[r] >= tau) << r;
+                    wave_sync();
+                    int pos = hits ? atomicAdd(&cnt[ct], (int)__popc(hits)) : 0;
 #pragma unroll
-                for (int r = 0; r < R; ++r)
-                    if ((hits >> r) & 1u) {
-                        if (pos < 4 * CPT) tl[pos] = keys[r];
-                        ++pos;
-                    }
-                wave_sync();
-                const int n = cnt[ct];
-                if (!__ballot(n > 4 * CPT)) {
+                    for (int r = 0; r < R; ++r)
+                        if ((hits >> r) & 1u) {
+                            if (pos < 4 * CPT) tl[pos] = keys[r];
+                            ++pos;
+                        }
+                    wave_sync();
+                    const int n = cnt[ct];
+                    if (__ballot(n > 4 * CPT)) break;
                     const uint64_t e = tl[lanepos];
                     int above = 0;
                     for (int f = 0; __ballot(f < n); f += 4) {
 #pragma unroll
                         for (int u = 0; u < 4; ++u) above += (int)(tl[f + u] > e);
                     }
-                    if (e != 0ull) placed[above] = e;
                     wave_sync();
-                    const uint64_t k = placed[lanepos];
+                    tl[lanepos] = none;
+                    wave_sync();
+                    if (e != 0ull) tl[above] = e;
+                    wave_sync();
+                    const uint64_t k = tl[lanepos];
                     const uint64_t full = __ballot(k != 0ull);
                     const int rank = (int)__popcll(full & before_mask), total = (int)__popcll(full & token_mask);
                     if (!__ballot(total < Kl && tau != 0u)) {
@@ -632,7 +638,18 @@ __global__ __launch_bounds__(kEncThreads, (X_BF16 && (CPT == 16 || CPT == 8) && 
                             }
                         }
                         done = true;
+                        break;
                     }
+                    if (again) break;
+                    // the K_l-th distinct lane maximum (equal ones are neighbours), 0 if there is none
+                    const uint32_t prev = (uint32_t)__builtin_amdgcn_ds_bpermute(prev_addr, (int)top[0]);
+                    const bool kept = top[0] != 0u && (lanepos == 0 || top[0] != prev);
+                    const int drank = (int)__popcll(__ballot(kept) & before_mask);
+                    const uint64_t owner = __ballot(kept && drank == Kl - 1) & token_mask;
+                    const uint32_t dtau =
+                        (uint32_t)__builtin_amdgcn_ds_bpermute((int)__builtin_ctzll(owner | (1ull << 63)) << 2, (int)top[0]);
+                    tau = owner ? dtau : 0u;
+                    wave_sync();
                 }
                 wave_sync();
             }
