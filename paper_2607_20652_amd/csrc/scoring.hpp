@@ -26,8 +26,8 @@ struct ActTile {
 };
 
 // Words 4 m, m < MW, of the sign bitmap of index pu (from the table row nt of
-// the first of them), two nibble groups at a time: the XOR of one table row per group (parity is linear in the index
-// bits; table layout [g][w][16]: word w of group g for nibble value v at
+// the first of them), two nibble groups at a time: the XOR of one table row
+// per group (parity is linear in the index bits; table layout [g][w][16]: word w of group g for nibble value v at
 // (g * nchunk + w) * 16 + v).  Every read has a fixed offset from its group's
 // address and each pair of groups folds in one instruction a word.
 template <int MW>
@@ -61,13 +61,14 @@ __device__ __forceinline__ void bitmap_words(const uint32_t* nt, int nchunk, int
 // (zero words for p < 0) and building words w0, w0 + 4, ....  Rows of whole
 // quadruples of words take bitmap_words (the parents' bitmaps were
 // 130 of the encoder's 3,866 vector instructions per level and group, 18 for
-// each nibble group); the rest read clamped words.
+// each nibble group); the rest, and every row without QUADS, read clamped words.
+template <bool QUADS = true>
 __device__ __forceinline__ void index_bitmaps(const DevPlan& P, int lane, int32_t p, const uint32_t* nt, uint32_t* cw)
 {
     const int nchunk = P.nchunk, w0 = lane >> 4, col = lane & 15;
     const uint32_t pu = p >= 0 ? (uint32_t)p : 0u;
     uint32_t* dst = cw + col * P.cws;
-    if ((nchunk & 3) == 0) {
+    if (QUADS && (nchunk & 3) == 0) {
         for (int wb = w0; wb < nchunk; wb += 32) {
             const uint32_t* t = nt + 16 * wb;
             switch (min(nchunk - wb + w0, 32) >> 2) {
@@ -108,13 +109,14 @@ __device__ __forceinline__ void index_bitmaps(const DevPlan& P, int lane, int32_
 // Sign bitmaps of the 16 columns of block nb: column r is parent slot
 // q = r mod 2^csh of token tt = r / 2^csh, with parent parents[tt * pstride + q]
 // when q < nparents and tt < ntok.
+template <bool QUADS = true>
 __device__ void column_bitmaps(const DevPlan& P, int lane, int ntok, int csh, int nb, const int32_t* parents,
                                int pstride, int nparents, const uint32_t* nt, uint32_t* cw)
 {
     const int r = nb * 16 + (lane & 15), tt = r >> csh, q = r & ((1 << csh) - 1);
     int32_t p = -1;
     if (r < (P.wave_tokens << csh) && tt < ntok && q < nparents) p = parents[tt * pstride + q];
-    index_bitmaps(P, lane, p, nt, cw);
+    index_bitmaps<QUADS>(P, lane, p, nt, cw);
 }
 
 // The column operands of fp32 activations: dword i pairs coordinates i and
