@@ -70,7 +70,9 @@ struct ColPlan {
 
 constexpr int kColWaves = 4;
 constexpr int kColThreads = 64 * kColWaves;
-// Waves per SIMD the kernels are held to by registers.
+// Waves per SIMD the kernels are held to by registers.  (The decode to fp32
+// with sixteen columns and more than 24 index bits keeps four of its registers
+// in scratch for it; with three waves, 16,381 tokens d 1024 N 2^28 103 -> 109 us.)
 constexpr int col_decode_waves(int cpt) { return cpt ? 4 : 8; }
 constexpr int col_bwd_waves(int cpt, bool g_bf16) { return cpt == 0 && g_bf16 ? 5 : 4; }   // (five in fp32: 60 us for 53)
 constexpr int kColMaxSlots = 254;   // a mark holds slot + 1 in a byte
@@ -461,8 +463,8 @@ __device__ __forceinline__ void col_stage_few(const ColPlan& C, const ColWave& W
 }
 
 // Coordinate steps of a pass (twice the steps take twice the registers of sums:
-// four tokens a wave have them).
-constexpr int col_pass_steps(int cpt) { return cpt == 4 ? 8 : 4; }
+// four tokens a wave have them up to 24 index bits).
+constexpr int col_pass_steps(int cpt, int ng) { return cpt == 4 && ng < 8 ? 8 : 4; }
 
 // Sums of the slots of W.xs (at most n per token) over the steps from m0 on,
 // as many words of them at a time as the plan's tables have room for.  The
@@ -472,9 +474,9 @@ constexpr int col_pass_steps(int cpt) { return cpt == 4 ? 8 : 4; }
 // the row-in-LDS kernels); backward 344, 143 (174).
 template <int CPT, int NG>
 __device__ __forceinline__ void col_pass(const ColPlan& C, const ColWave& W, const float* cf, int n, int m0,
-                                         float (&ex)[2 * col_pass_steps(CPT)])
+                                         float (&ex)[2 * col_pass_steps(CPT, NG)])
 {
-    constexpr int LPT = 64 / col_tpw(CPT), PS = col_pass_steps(CPT);
+    constexpr int LPT = 64 / col_tpw(CPT), PS = col_pass_steps(CPT, NG);
     const uint32_t vb = lds_addr(W.tab) + (uint32_t)(W.lane / LPT * C.words) * 1024u;
     const u32x4* mk = W.mask + (W.lane & (LPT - 1));
 #pragma unroll
@@ -533,7 +535,7 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
     const bool even = (C.d & 1) == 0;
     const float* bas = W.bas + tt * (C.k + 1);
     u32x4 B[NP];
-    const int mend = PASS ? min(m0 + col_pass_steps(CPT), C.steps) : C.steps;
+    const int mend = PASS ? min(m0 + col_pass_steps(CPT, NG), C.steps) : C.steps;
     fetch(PASS ? m0 : 0, B);
     for (int m = PASS ? m0 : 0; m < mend; ++m) {
         const u32x4 sm = mk[m * LPT];
@@ -563,7 +565,7 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
             t[0] += ex[0];
             t[1] += ex[1];
 #pragma unroll
-            for (int u = 0; u + 2 < 2 * col_pass_steps(CPT); ++u) ex[u] = ex[u + 2];
+            for (int u = 0; u + 2 < 2 * col_pass_steps(CPT, NG); ++u) ex[u] = ex[u + 2];
         }
 #pragma unroll
         for (int e = 0; e < 2; ++e) U[e] = col_word<NG>(vb, s0[e], s1[e]);
@@ -725,8 +727,8 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
         // the tables hold the unlisted slots of a few steps and the listed ones
         // of the same steps in turn
         ColWave V = W;
-        for (int m0 = 0; m0 < C.steps; m0 += col_pass_steps(CPT)) {
-            float ex[2 * col_pass_steps(CPT)];
+        for (int m0 = 0; m0 < C.steps; m0 += col_pass_steps(CPT, NG)) {
+            float ex[2 * col_pass_steps(CPT, NG)];
             __asm__ volatile("" : "+v"(V.lane));   // nothing of this path is worked out before it
             col_pass<CPT, NG>(C, V, cf, nx, m0, ex);
             __asm__ volatile("" : "+v"(V.lane));
