@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <vector>
 
@@ -177,18 +178,20 @@ inline void allow_lds(F* kernel, size_t bytes)
         (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-// Compute units of the current device (asked once: the answer sizes grids only).
+// Compute units of the current device, asked once per device (the answer sizes
+// grids only; asking costs a copy of the device's properties per launch).
 inline int device_cus()
 {
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            cus = prop.multiProcessorCount;
-        if (cus <= 0) cus = 256;
-    }
-    return cus;
+    constexpr int kDevices = 64, kDefault = 256;
+    static std::atomic<int> cus[kDevices];   // 0: not asked yet
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return kDefault;
+    const bool kept = dev >= 0 && dev < kDevices;
+    if (kept) n = cus[dev].load(std::memory_order_relaxed);
+    if (n) return n;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return kDefault;
+    if (kept) cus[dev].store(n, std::memory_order_relaxed);
+    return n;
 }
 
 // True when the general encoder's workgroup (one fp32 token) fits the LDS budget.

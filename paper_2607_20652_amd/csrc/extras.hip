@@ -749,23 +749,10 @@ __global__ void var_grad_kernel(int64_t n, VarWs W, float* grad, const float* gr
         grad[s] = w * W.pre[s];
 }
 
-int device_cus_x()
-{
-    static int cus = 0;
-    if (!cus) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
-            cus = prop.multiProcessorCount;
-        if (cus <= 0) cus = 256;
-    }
-    return cus;
-}
-
 dim3 row_grid(int64_t T)
 {
     const int64_t need = (T + kRowWaves - 1) / kRowWaves;
-    return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)device_cus_x() * 8)));
+    return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)device_cus() * 8)));
 }
 
 // Register chunks of 512 elements per row: 1, 2 or 4 (d <= 2048), else 0.
@@ -778,7 +765,7 @@ int row_chunks(int d)
 dim3 flat_grid(int64_t n, int threads)
 {
     const int64_t need = (n + threads - 1) / threads;
-    return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)device_cus_x() * 16)));
+    return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)device_cus() * 16)));
 }
 
 }  // namespace
