@@ -462,9 +462,7 @@ __device__ __forceinline__ void col_stage_few(const ColPlan& C, const ColWave& W
     wave_sync();
 }
 
-// Coordinate steps of a pass (twice the steps take twice the registers of sums:
-// four tokens a wave have them up to 24 index bits).
-constexpr int col_pass_steps(int cpt, int ng) { return cpt == 4 && ng < 8 ? 8 : 4; }
+constexpr int kColPass = 4;   // coordinate steps of a pass
 
 // Sums of the slots of W.xs (at most n per token) over the steps from m0 on,
 // as many words of them at a time as the plan's tables have room for.  The
@@ -474,9 +472,9 @@ constexpr int col_pass_steps(int cpt, int ng) { return cpt == 4 && ng < 8 ? 8 : 
 // the row-in-LDS kernels); backward 344, 143 (174).
 template <int CPT, int NG>
 __device__ __forceinline__ void col_pass(const ColPlan& C, const ColWave& W, const float* cf, int n, int m0,
-                                         float (&ex)[2 * col_pass_steps(CPT, NG)])
+                                         float (&ex)[2 * kColPass])
 {
-    constexpr int LPT = 64 / col_tpw(CPT), PS = col_pass_steps(CPT, NG);
+    constexpr int LPT = 64 / col_tpw(CPT), PS = kColPass;
     const uint32_t vb = lds_addr(W.tab) + (uint32_t)(W.lane / LPT * C.words) * 1024u;
     const u32x4* mk = W.mask + (W.lane & (LPT - 1));
 #pragma unroll
@@ -491,8 +489,21 @@ __device__ __forceinline__ void col_pass(const ColPlan& C, const ColWave& W, con
             for (int u = 0; u < PS; ++u) {
                 const u32x4 sm = mk[min(m0 + u, C.steps - 1) * LPT];
                 const uint32_t v = vb + (uint32_t)w * 1024u;
-                ex[2 * u] = col_word_sum(v + 512u, col_word<NG>(v, sm.x, sm.y), ex[2 * u]);
-                ex[2 * u + 1] = col_word_sum(v + 512u, col_word<NG>(v, sm.z, sm.w), ex[2 * u + 1]);
+                const uint32_t x[2] = {col_word<NG>(v, sm.x, sm.y), col_word<NG>(v, sm.z, sm.w)};
+                float r[2][8];   // all sixteen requested before the first is added
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const uint32_t e4 = (x[e] << 2) & 0x3C3C3C3Cu, o4 = (x[e] >> 2) & 0x3C3C3C3Cu;
+#pragma unroll
+                    for (int n = 0; n < 8; ++n)
+                        r[e][n] = lds_ldf(__builtin_amdgcn_perm(v + 512u, (n & 1) ? o4 : e4, 0x07060500u | (uint32_t)(n >> 1)) +
+                                          (uint32_t)(n * 64));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int n = 0; n < 8; ++n) ex[2 * u + e] += r[e][n];
             }
         }
         wave_sync();
@@ -535,7 +546,7 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
     const bool even = (C.d & 1) == 0;
     const float* bas = W.bas + tt * (C.k + 1);
     u32x4 B[NP];
-    const int mend = PASS ? min(m0 + col_pass_steps(CPT, NG), C.steps) : C.steps;
+    const int mend = PASS ? min(m0 + kColPass, C.steps) : C.steps;
     fetch(PASS ? m0 : 0, B);
     for (int m = PASS ? m0 : 0; m < mend; ++m) {
         const u32x4 sm = mk[m * LPT];
@@ -565,7 +576,7 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
             t[0] += ex[0];
             t[1] += ex[1];
 #pragma unroll
-            for (int u = 0; u + 2 < 2 * col_pass_steps(CPT, NG); ++u) ex[u] = ex[u + 2];
+            for (int u = 0; u + 2 < 2 * kColPass; ++u) ex[u] = ex[u + 2];
         }
 #pragma unroll
         for (int e = 0; e < 2; ++e) U[e] = col_word<NG>(vb, s0[e], s1[e]);
@@ -727,8 +738,8 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
         // the tables hold the unlisted slots of a few steps and the listed ones
         // of the same steps in turn
         ColWave V = W;
-        for (int m0 = 0; m0 < C.steps; m0 += col_pass_steps(CPT, NG)) {
-            float ex[2 * col_pass_steps(CPT, NG)];
+        for (int m0 = 0; m0 < C.steps; m0 += kColPass) {
+            float ex[2 * kColPass];
             __asm__ volatile("" : "+v"(V.lane));   // nothing of this path is worked out before it
             col_pass<CPT, NG>(C, V, cf, nx, m0, ex);
             __asm__ volatile("" : "+v"(V.lane));
