@@ -294,30 +294,22 @@ __device__ __forceinline__ float column_sum(bf16x4 ahi, bf16x4 amid, bf16x4 alo,
     return column_signs(column_acc<EXACT3>(ahi, amid, alo, bfe), pv);
 }
 
-// Leaf columns when every lane's column belongs to a live token (CPT
-// parents, 16 / CPT tokens, all present): each lane of a token's group
-// writes the same sum, so there are no masked stores or branches and the
+// Leaf columns of sixteen parents, one token a wave: every lane of the token's
+// group writes the same sum, so there are no masked stores or branches and the
 // compiler overlaps the NB columns of a batch.
-template <int CPT, bool EXACT3, bool PB16, int NB>
-__device__ __forceinline__ void leaf_columns(const DevPlan& P, const Wave& W, bf16x4 ahi, bf16x4 amid, bf16x4 alo)
+template <bool EXACT3, int NB>
+__device__ __forceinline__ void leaf_columns16(const DevPlan& P, const Wave& W, bf16x4 ahi, bf16x4 amid, bf16x4 alo)
 {
-    constexpr int CSH = CPT == 4 ? 2 : CPT == 8 ? 3 : 4;
     const int L1 = P.levels - 1, dp = P.dp, lane = W.lane;
     const int row = lane & 15, grp = lane >> 4;
     const u32x2* bfr = (const u32x2*)P.gamma_t + P.gamma_t_off[L1] + lane;
-    const int tok = (4 * grp) >> CSH, q0 = (4 * grp) & (CPT - 1);
-    const int pbo = tok * dp + row;
-    float* yt = W.y + pbo;
+    float* yt = W.y + row;
     const int x32 = ((lane ^ 32) << 2);
     const int ncb = dp / 16;
-    auto pb_at = [&](int cb) -> uint32_t {
-        if constexpr (PB16) return (uint32_t)((const uint16_t*)W.pb)[pbo + 16 * cb] >> q0;
-        else return (uint32_t)((const uint8_t*)W.pb)[pbo + 16 * cb] >> q0;
-    };
+    auto pb_at = [&](int cb) -> uint32_t { return (uint32_t)((const uint16_t*)W.pb)[row + 16 * cb] >> (4 * grp); };
     auto token_sum = [&](float v) {
-        if constexpr (CPT >= 8) v += swz_xorf16(v);
-        if constexpr (CPT >= 16) v += __int_as_float(__builtin_amdgcn_ds_bpermute(x32, __float_as_int(v)));
-        return v;
+        v += swz_xorf16(v);
+        return v + __int_as_float(__builtin_amdgcn_ds_bpermute(x32, __float_as_int(v)));
     };
     int cb0 = 0;
     for (; cb0 + NB <= ncb; cb0 += NB) {
@@ -475,17 +467,10 @@ __device__ void decode_tokens(const DevPlan& P, const Wave& W, const float* cf)
     }
 
     if (cols) {
-        // Gamma^T alpha on the matrix cores, then the parents' signs.  With
-        // every column a live token's (full waves of two tokens of eight
-        // parents) all lanes write.
-        const int CPT = P.cpt[L1];
-        const bool all = TPW * CPT == 16 && W.ntok == TPW;
-        // (one compile-time layout per kernel variant: more of them inlined here
-        // cost the kernels registers, and with them a wave per SIMD.  Eight
-        // parents per token take one byte of sign bits (PB16 false), sixteen
-        // take two: one token per wave, all sixteen columns its own)
-        if (!PB16 && CPT == 8 && all) leaf_columns<8, EXACT3, PB16, LCB>(P, W, ahi, amid, alo);
-        else if (PB16 && CPT == 16 && all) leaf_columns<16, EXACT3, PB16, LCB>(P, W, ahi, amid, alo);
+        // Gamma^T alpha on the matrix cores, then the parents' signs (sixteen
+        // parents take two bytes of sign bits; one compile-time layout per kernel
+        // variant: more of them cost registers, and with them a wave per SIMD)
+        if (PB16 && P.cpt[L1] == 16 && TPW == 1) leaf_columns16<EXACT3, LCB>(P, W, ahi, amid, alo);
         else leaf_columns_any<EXACT3, PB16>(P, W, ahi, amid, alo);
         wave_sync();
     }
@@ -665,21 +650,18 @@ __global__ __launch_bounds__(kThreads) void decode2_kernel(DevPlan P, const int3
     Wave W = make_wave(P, smem, false, true, wave, lane);
     const int64_t ngroups = (T + TPW - 1) / TPW;
     const int64_t gstride = (int64_t)gridDim.x * kCodeWaves;
-    // the next group's code is requested while this group is decoded (two
-    // tokens of at most 128 slots or one of at most 256: four words of each
-    // array per lane)
+    // the next token's code is requested while this one is decoded (at most
+    // 256 slots: four words of each array per lane)
     constexpr int kPrefetch = 4;
-    const bool pf = (TPW == 2 && k <= 128) || (TPW == 1 && k <= 256);
+    const bool pf = TPW == 1 && k <= 64 * kPrefetch;
     int32_t nidx[kPrefetch];
     float ncoef[kPrefetch];
     auto fetch = [&](int64_t grp) {
 #pragma unroll
         for (int e = 0; e < kPrefetch; ++e) {
-            const int tt = TPW == 2 ? e >> 1 : 0, s = (TPW == 2 ? (e & 1) : e) * 64 + lane;
-            const int64_t t = grp * TPW + tt;
-            const bool ok = s < k && t < T;
-            nidx[e] = ok ? idx[t * k + s] : -1;
-            ncoef[e] = ok ? coef[t * k + s] : 0.f;
+            const int s = e * 64 + lane;
+            nidx[e] = s < k ? idx[grp * k + s] : -1;
+            ncoef[e] = s < k ? coef[grp * k + s] : 0.f;
         }
     };
     int64_t grp = (int64_t)blockIdx.x * kCodeWaves + wave;
@@ -690,11 +672,11 @@ __global__ __launch_bounds__(kThreads) void decode2_kernel(DevPlan P, const int3
         if (pf) {
 #pragma unroll
             for (int e = 0; e < kPrefetch; ++e) {
-                const int tt = TPW == 2 ? e >> 1 : 0, s = (TPW == 2 ? (e & 1) : e) * 64 + lane;
+                const int s = e * 64 + lane;
                 if (s < k) {
-                    W.idx[tt * k + s] = nidx[e];
-                    W.coef[tt * k + s] = ncoef[e];
-                    W.route[tt * k + s] = -1;
+                    W.idx[s] = nidx[e];
+                    W.coef[s] = ncoef[e];
+                    W.route[s] = -1;
                 }
             }
             if (grp + gstride < ngroups) fetch(grp + gstride);
@@ -728,13 +710,13 @@ __global__ __launch_bounds__(kThreads) void decode_bwd2_kernel(DevPlan P, const 
     const int64_t ngroups = (T + TPW - 1) / TPW;
     const int64_t gstride = (int64_t)gridDim.x * kCodeWaves;
     // the next group's code is requested while this group is processed
-    // (two tokens of at most 128 slots: four words per lane)
-    const bool pf = TPW == 2 && k <= 128;
+    // (four words per lane: one token of at most 256 slots, in fp32 two of at most 128)
+    const bool pf = G_BF16 ? TPW == 1 && k <= 256 : TPW == 2 && k <= 128;
     int32_t nidx[4];
     auto fetch = [&](int64_t gp) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int tt = e >> 1, s = (e & 1) * 64 + lane;
+            const int tt = G_BF16 ? 0 : e >> 1, s = (G_BF16 ? e : (e & 1)) * 64 + lane;
             const int64_t t = gp * TPW + tt;
             nidx[e] = (s < k && t < T) ? idx[t * k + s] : -1;
         }
@@ -750,7 +732,7 @@ __global__ __launch_bounds__(kThreads) void decode_bwd2_kernel(DevPlan P, const 
         if (pf) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int tt = e >> 1, s = (e & 1) * 64 + lane;
+                const int tt = G_BF16 ? 0 : e >> 1, s = (G_BF16 ? e : (e & 1)) * 64 + lane;
                 if (s < k) {
                     W.idx[tt * k + s] = nidx[e];
                     W.route[tt * k + s] = -1;
