@@ -94,10 +94,14 @@ static void launch_col_ng(int ng, const ColPlan& C, size_t lds, hipStream_t stre
 template <bool OB>
 static bool launch_col(const DevPlan& P, const int32_t* idx, const float* coef, int64_t T, void* y, hipStream_t stream)
 {
-    const int cpt = col_cpt(P);
+    auto lds_bytes = [&](int cpt) {
+        const ColPlan C = col_plan(P, cpt);
+        return col_shared_bytes(C) + (size_t)kColWaves * col_layout(C, cpt, 0).bytes;
+    };
+    const int cpt = col_choose(P, lds_bytes);
     if (cpt < 0) return false;
     const ColPlan C = col_plan(P, cpt);
-    const size_t lds = col_shared_bytes(C) + (size_t)kColWaves * col_layout(C, cpt, 0).bytes;
+    const size_t lds = lds_bytes(cpt);
     if (lds > (size_t)kLdsBudget) return false;
     const int ng = ng_variant(P);
     if (cpt == 0) launch_col_ng<0, OB>(ng, C, lds, stream, idx, coef, T, y);

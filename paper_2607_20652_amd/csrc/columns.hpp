@@ -880,6 +880,25 @@ inline ColPlan col_plan(const DevPlan& P, int cpt)
     return C;
 }
 
+// The parent columns per token a kernel takes for the plan (lds(cpt): bytes of
+// its workgroup).  A wave of several tokens holds all their rows.  Where a CU
+// has room for one such workgroup only, and for two or more without leaf
+// columns, the plan goes without them unless they save it table words; where
+// it has room for none, it goes without them in any case (else the row-in-LDS
+// kernels would take it).
+// Backward of 16,381 tokens in bf16, us, with and without: d 1024 K 32,32,4,12
+// 324 and 102, d 2048 K 4,4,8 168 and 101, d 3000 K 8,8,16 347 and 287; a word
+// more without: d 2048 K 4,4,32 178 and 224; one workgroup either way: d 4096
+// K 8,8,16 418 and 564.
+template <typename Lds>
+inline int col_choose(const DevPlan& P, Lds lds)
+{
+    const int cpt = col_cpt(P);
+    if (cpt <= 0 || lds(cpt) <= (size_t)kLdsBudget / 2) return cpt;
+    if (lds(cpt) > (size_t)kLdsBudget) return 0;
+    return lds(0) <= (size_t)kLdsBudget / 2 && col_plan(P, 0).words <= col_plan(P, cpt).words ? 0 : cpt;
+}
+
 // Persistent grid over groups of `tpw` tokens: `rounds` times the workgroups
 // that `lds` lets the chip hold, at most `waves` waves per SIMD of them.
 inline dim3 col_grid(int64_t T, int tpw, size_t lds, int waves, int rounds)

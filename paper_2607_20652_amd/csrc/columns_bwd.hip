@@ -293,13 +293,16 @@ template <bool GB, bool XB>
 static bool launch_colb(const DevPlan& Pp, const int32_t* idx, const void* g, int64_t T, float* gc, void* gx,
                            BwdExtra ex, hipStream_t stream)
 {
-    const int cpt = col_cpt(Pp);
-    if (cpt < 0) return false;
     DevPlan P = Pp;
-    P.wave_tokens = col_tpw(cpt);
+    auto lds_bytes = [&](int cpt) {
+        P.wave_tokens = col_tpw(cpt);
+        const ColPlan C = col_plan(P, cpt);
+        return col_shared_bytes(C) + (size_t)kColWaves * col_layout(C, cpt, col_act_bytes(P, cpt, GB)).bytes;
+    };
+    const int cpt = col_choose(Pp, lds_bytes);
+    if (cpt < 0) return false;
+    const size_t lds = lds_bytes(cpt);   // leaves its tokens a wave in P
     const ColPlan C = col_plan(P, cpt);
-    const size_t lds =
-        col_shared_bytes(C) + (size_t)kColWaves * col_layout(C, cpt, col_act_bytes(P, cpt, GB)).bytes;
     if (lds > (size_t)kLdsBudget) return false;
     const int ng = ng_variant(P);
     if (cpt == 0) launch_colb_ng<0, GB, XB>(ng, C, P, lds, stream, idx, g, T, gc, gx, ex);

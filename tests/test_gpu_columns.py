@@ -42,6 +42,12 @@ PLANS = {
     "table_odd": (333, (9, 13, 17), (16, 16, 16), 16),       # 32 slots: one full word
     "table_254": (512, (9, 13, 17), (16, 110, 128), 64),     # the widest code of marks
     "one_level": (300, (9,), (20,), 16),
+    # four parents under a wide beam: rows of four tokens leave a CU one workgroup, so these go without columns
+    "few_parents": (1024, (10, 13, 16, 20), (32, 32, 4, 12)),           # the backward
+    "few_parents_d1500": (1500, (11, 14, 17, 20), (32, 32, 4, 12)),     # the decode too
+    "few_parents_d2048": (2048, (11, 14, 17), (4, 4, 8)),
+    "few_parents_d4096": (4096, (12, 14, 16), (4, 4, 8)),               # rows of four tokens do not fit
+    "four_of_2048": (2048, (11, 14, 17), (4, 4, 32)),                   # columns save a word: kept
     "table_k0": (300, (9, 13), (100, 64), 64),               # up to 100 hashed indices on level 0
 }
 
