@@ -1,7 +1,8 @@
 // Decode and decode-backward for gfx950, with the rows in LDS: the kernels of
-// plans that the column kernels (columns.hpp) do not take, codes wider than 254
-// slots and wide rows whose column layout does not fit a CU.  Every other plan
-// runs faster there (1.2 to 2.5 times on the shapes measured).
+// codes wider than 254 slots, which the column kernels (columns.hpp) do not
+// take (a mark there holds slot + 1 in a byte).  Every valid plan of narrower
+// codes fits the column kernels and runs faster there: whole codes 1.2 to 4
+// times on the shapes measured.
 //
 // A code slot c of level l >= 1 is a child p XOR g_j of some parent p in the
 // previous level, and its direction factorises as phi~_c = phi~_p (.) gamma_j
@@ -710,15 +711,14 @@ __global__ __launch_bounds__(kThreads) void decode_bwd2_kernel(DevPlan P, const 
     const int64_t ngroups = (T + TPW - 1) / TPW;
     const int64_t gstride = (int64_t)gridDim.x * kCodeWaves;
     // the next group's code is requested while this group is processed
-    // (four words per lane: one token of at most 256 slots, in fp32 two of at most 128)
-    const bool pf = G_BF16 ? TPW == 1 && k <= 256 : TPW == 2 && k <= 128;
+    // (bf16, one token of at most 256 slots: four words per lane)
+    const bool pf = G_BF16 && TPW == 1 && k <= 256;
     int32_t nidx[4];
     auto fetch = [&](int64_t gp) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int tt = G_BF16 ? 0 : e >> 1, s = (G_BF16 ? e : (e & 1)) * 64 + lane;
-            const int64_t t = gp * TPW + tt;
-            nidx[e] = (s < k && t < T) ? idx[t * k + s] : -1;
+            const int s = e * 64 + lane;
+            nidx[e] = s < k ? idx[gp * k + s] : -1;
         }
     };
     int64_t grp = (int64_t)blockIdx.x * kCodeWaves + wave;
@@ -732,10 +732,10 @@ __global__ __launch_bounds__(kThreads) void decode_bwd2_kernel(DevPlan P, const 
         if (pf) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int tt = G_BF16 ? 0 : e >> 1, s = (G_BF16 ? e : (e & 1)) * 64 + lane;
+                const int s = e * 64 + lane;
                 if (s < k) {
-                    W.idx[tt * k + s] = nidx[e];
-                    W.route[tt * k + s] = -1;
+                    W.idx[s] = nidx[e];
+                    W.route[s] = -1;
                 }
             }
             if (grp + gstride < ngroups) fetch(grp + gstride);
