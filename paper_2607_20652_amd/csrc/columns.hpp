@@ -380,14 +380,30 @@ __device__ __forceinline__ float col_word_sum(uint32_t tb, uint32_t x, float t)
     return t;
 }
 
+// Unlisted slots of a token up to which they are added one by one: about ten
+// vector instructions a slot and step, against a table set-up per pass and
+// one instruction a slot.  Decode of 16,381 tokens d 768 k 96, us, one by one
+// and in passes: 8 slots 55 and 69, 16 slots 67 and 68, 32 slots 84 and 65; at
+// d 4096 k 80 (two waves a CU, where the set-ups' latency shows) 32 slots 685
+// and 785.  Without leaf columns all of them are added one by one: they are
+// hashed indices on level 0 alone.
+constexpr int col_few(int cpt) { return cpt ? 16 : 1 << 30; }
+
+// Unlisted slots of a wave's tokens: the most of a token that has its added
+// one by one, the most of the others (bits of `big`).  Each token's way, and so
+// the order of its sums, is its own count's alone.
+struct Unlisted {
+    int few, many;
+    uint32_t big;
+};
+
 // Marks the basis slots' coordinates with slot + 1 and keeps their
 // coefficients by mark in W.bas (a coordinate held by several slots gathers
 // their coefficients, in slot order, in the marked one); lists the slots that
-// fit nowhere else in W.xs and returns the largest number of them any token
-// has.  (Leaf slots that went into their parent's column hold a negative index
-// by now.)
+// fit nowhere else in W.xs and returns how many of them there are.  (Leaf slots
+// that went into their parent's column hold a negative index by now.)
 template <int CPT>
-__device__ __forceinline__ int col_marks(const ColPlan& C, const ColWave& W, const float* cf)
+__device__ __forceinline__ Unlisted col_marks(const ColPlan& C, const ColWave& W, const float* cf)
 {
     constexpr int TPW = col_tpw(CPT);
     const int lane = W.lane, k = C.k;
@@ -422,8 +438,8 @@ __device__ __forceinline__ int col_marks(const ColPlan& C, const ColWave& W, con
         }
         wave_sync();
     }
-    if (!extras) return 0;
-    int most = 0;
+    Unlisted U{0, 0, 0u};
+    if (!extras) return U;
     for (int tt = 0; tt < TPW; ++tt) {
         int n = 0;
         for (int s0 = 0; s0 < k; s0 += 64) {
@@ -434,28 +450,26 @@ __device__ __forceinline__ int col_marks(const ColPlan& C, const ColWave& W, con
             n += (int)__popcll(ball);
         }
         for (int i = n + lane; i < k; i += 64) W.xs[tt * k + i] = 0xFFFF;   // no slot
-        most = max(most, n);
+        if (n > col_few(CPT)) {
+            U.many = max(U.many, n);
+            U.big |= 1u << tt;
+        } else {
+            U.few = max(U.few, n);
+        }
     }
     wave_sync();
-    return most;
+    return U;
 }
 
-// Unlisted slots of a token up to which they are added one by one: about ten
-// vector instructions a slot and step, against a table set-up per pass and
-// one instruction a slot.  Decode of 16,381 tokens d 768 k 96, us, one by one
-// and in passes: 8 slots 55 and 69, 16 slots 67 and 68, 32 slots 84 and 65; at
-// d 4096 k 80 (two waves a CU, where the set-ups' latency shows) 32 slots 685
-// and 785.  Without leaf columns all of them are added one by one: they are
-// hashed indices on level 0 alone.
-constexpr int col_few(int cpt) { return cpt ? 16 : 1 << 30; }
-
 // Index and scaled coefficient of the 64 / TPW slots of W.xs from number i0
-// on, zero past the last, where the tables' scratch is free by now.
+// on, zero past the last and for the tokens of `big`, where the tables'
+// scratch is free by now.
 template <int CPT>
-__device__ __forceinline__ void col_stage_few(const ColPlan& C, const ColWave& W, const float* cf, int i0)
+__device__ __forceinline__ void col_stage_few(const ColPlan& C, const ColWave& W, const float* cf, int i0, uint32_t big)
 {
     constexpr int cap = 64 / col_tpw(CPT);
-    const int lane = W.lane, i = i0 + (lane & (cap - 1)), tt = lane / cap, s = i < C.k ? W.xs[tt * C.k + i] : 0xFFFF;
+    const int lane = W.lane, i = i0 + (lane & (cap - 1)), tt = lane / cap;
+    const int s = i < C.k && !((big >> tt) & 1u) ? W.xs[tt * C.k + i] : 0xFFFF;
     const int at = tt * C.k + (s == 0xFFFF ? 0 : s);
     const float a = s == 0xFFFF ? 0.f : C.rsd * cf[at];
     ((u32x2*)W.scr)[lane] = u32x2{(uint32_t)W.idx[at], __float_as_uint(a)};
@@ -464,14 +478,14 @@ __device__ __forceinline__ void col_stage_few(const ColPlan& C, const ColWave& W
 
 constexpr int kColPass = 4;   // coordinate steps of a pass
 
-// Sums of the slots of W.xs (at most n per token) over the steps from m0 on,
+// Sums of the slots of W.xs of U's big tokens over the steps from m0 on,
 // as many words of them at a time as the plan's tables have room for.  The
 // tables are built anew for each pass, the plan's own after them: room for
 // both would take a workgroup a CU from every code.  A code of 64 leaves and
 // no parent, 16,381 tokens d 768, us: decode 254 one by one, 80 here (108 in
 // the row-in-LDS kernels); backward 344, 143 (174).
 template <int CPT, int NG>
-__device__ __forceinline__ void col_pass(const ColPlan& C, const ColWave& W, const float* cf, int n, int m0,
+__device__ __forceinline__ void col_pass(const ColPlan& C, const ColWave& W, const float* cf, Unlisted U, int m0,
                                          float (&ex)[2 * kColPass])
 {
     constexpr int LPT = 64 / col_tpw(CPT), PS = kColPass;
@@ -479,12 +493,12 @@ __device__ __forceinline__ void col_pass(const ColPlan& C, const ColWave& W, con
     const u32x4* mk = W.mask + (W.lane & (LPT - 1));
 #pragma unroll
     for (int u = 0; u < 2 * PS; ++u) ex[u] = 0.f;
-    for (int i0 = 0; i0 < n; i0 += 32 * C.words) {
+    for (int i0 = 0; i0 < U.many; i0 += 32 * C.words) {
         col_tables<CPT, NG>(C, W, cf, [&](int tt, int w, int b, bool&) {
-            const int i = i0 + 32 * w + b, s = i < C.k ? W.xs[tt * C.k + i] : 0xFFFF;
+            const int i = i0 + 32 * w + b, s = i < C.k && ((U.big >> tt) & 1u) ? W.xs[tt * C.k + i] : 0xFFFF;
             return s == 0xFFFF ? -1 : s;
         });
-        for (int w = 0; w < min(C.words, (n - i0 + 31) / 32); ++w) {
+        for (int w = 0; w < min(C.words, (U.many - i0 + 31) / 32); ++w) {
 #pragma unroll
             for (int u = 0; u < PS; ++u) {
                 const u32x4 sm = mk[min(m0 + u, C.steps - 1) * LPT];
@@ -655,7 +669,7 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
             }
             y[e] = __builtin_fmaf(C.rsd, leaf, t[e]);
         }
-        if (!PASS && nx) {
+        if (nx) {
             // slots added one by one: sign = parity of the row mask and the index
             const uint32_t M0 = (s0[0] >> 2) | (s1[0] << 2), M1 = (s0[1] >> 2) | (s1[1] << 2);
             auto add_slot = [&](uint32_t c, float a) {
@@ -667,7 +681,7 @@ __device__ __forceinline__ void col_steps(const ColPlan& C, const ColWave& W, co
             for (int i0 = 0; i0 < nx; i0 += cap) {
                 if (CPT == 0 && nx > cap) {   // more than the scratch holds
                     wave_sync();
-                    col_stage_few<CPT>(C, W, cf, i0);
+                    col_stage_few<CPT>(C, W, cf, i0, 0u);
                 }
                 for (int i = 0; i < min(nx - i0, cap); i += 4) {
                     u32x2 q[4];
@@ -733,25 +747,27 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
         wave_sync();
     }
     constexpr int MG = col_word0_slots(CPT) / 4;   // groups of word 0
-    const int nx = col_marks<CPT>(C, W, cf);
-    if (CPT > 0 && nx > col_few(CPT)) {
+    const Unlisted U = col_marks<CPT>(C, W, cf);
+    const int nx = U.few;
+    if (CPT > 0 && U.many) {
         // the tables hold the unlisted slots of a few steps and the listed ones
         // of the same steps in turn
         ColWave V = W;
         for (int m0 = 0; m0 < C.steps; m0 += kColPass) {
             float ex[2 * kColPass];
             __asm__ volatile("" : "+v"(V.lane));   // nothing of this path is worked out before it
-            col_pass<CPT, NG>(C, V, cf, nx, m0, ex);
+            col_pass<CPT, NG>(C, V, cf, U, m0, ex);
             __asm__ volatile("" : "+v"(V.lane));
             col_list_tables<CPT, NG>(C, V, cf);
+            if (nx) col_stage_few<CPT>(C, V, cf, 0, U.big);
             __asm__ volatile("" : "+v"(V.lane));
-            col_steps<CPT, NG, OUT_BF16, MG, true>(C, V, cf, F, c0, 0, row0, out, add, m0, ex);
+            col_steps<CPT, NG, OUT_BF16, MG, true>(C, V, cf, F, c0, nx, row0, out, add, m0, ex);
             wave_sync();
         }
         return;
     }
     col_list_tables<CPT, NG>(C, W, cf);
-    if (nx) col_stage_few<CPT>(C, W, cf, 0);
+    if (nx) col_stage_few<CPT>(C, W, cf, 0, 0u);
     wave_sync();
     const int g0 = min(C.ns, col_word0_slots(CPT));
     if (g0 == 0) col_steps<CPT, NG, OUT_BF16, 0>(C, W, cf, F, c0, nx, row0, out, add);

@@ -227,6 +227,50 @@ def test_unlisted_slots(name):
         compare_dense(gx.cpu().numpy(), rgx, TOL_F32)
 
 
+# enough rows that every wave of the persistent grids takes several groups
+STREAMED = {"cpt4_d200": 60000, "odd_d": 40000, "cpt16": 24000, "many_words": 24000, "cpt8": 40000, "few_parents": 24000,
+            "table_3l": 24000, "table_k0": 24000, "wide_code": 24000}
+
+
+@pytest.mark.parametrize("name", list(STREAMED))
+def test_streamed_groups_match_single_ones(name):
+    """Codes of every kind, shuffled and repeated over so many groups that each
+    wave goes on to further ones (the prefetched codes and gradient rows, the
+    marks, tables and columns a group leaves behind): every copy of a row is
+    within the bar of the oracle's, and all copies decode to the same bits,
+    whichever tokens share their waves."""
+    d, nb, K = PLANS[name][:3]
+    T, n = STREAMED[name], 23
+    print(f"[streamed] {name} T={T}", flush=True)
+    plan = dpb.Plan(d, seed=0, level_bits=list(nb), branchings=[0] + [branch(name)] * (len(nb) - 1), active=list(K))
+    idx, coef = codes(name, n, 9000 + d)
+    pick = torch.from_numpy(np.random.default_rng(9900 + d).integers(0, n, T)).to(DEV)
+    di, dc = torch.from_numpy(idx).to(DEV), torch.from_numpy(coef).to(DEV)
+    bi, bc = di[pick].contiguous(), dc[pick].contiguous()
+    m = oracle.masks(d, nb[-1])
+    ref = torch.from_numpy(oracle.decode(d, m, idx, coef.astype(np.float64))).to(DEV)
+
+    def check(got, want, tol):
+        want = want.to(DEV)
+        den = torch.maximum(want.abs(), want.square().mean(-1, keepdim=True).sqrt())
+        den = torch.where(den == 0, torch.ones_like(den), den)
+        for lo in range(0, T, 8192):
+            p = pick[lo:lo + 8192]
+            err = ((got[lo:lo + 8192].double() - want[p]).abs() / den[p]).max()
+            assert err <= tol, (lo, float(err))
+
+    for dt, tol in ((torch.float32, TOL_F32), (torch.bfloat16, TOL_BF16)):
+        y = dpb.decode(plan, bi, bc, dt)
+        check(y, ref, tol)
+        first = torch.zeros(n, dtype=torch.long, device=DEV).scatter_(0, pick.flip(0), torch.arange(T - 1, -1, -1, device=DEV))
+        assert torch.equal(y, y[first][pick])            # copies of a row agree wherever they stand
+        g = inputs.normal((n, d), 9100 + d, "f32").to(dt)
+        rgc, rgx = oracle.decode_bwd(d, m, idx, g.double().numpy())
+        gc, gx = dpb.decode_bwd(plan, bi, g.to(DEV)[pick].contiguous(), gx_dtype=dt)
+        check(gc, torch.from_numpy(rgc), TOL_F32)
+        check(gx, torch.from_numpy(rgx), tol)
+
+
 def _call_us(fn, reps=9, inner=4):
     for _ in range(3):
         fn()
