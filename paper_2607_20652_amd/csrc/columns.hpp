@@ -747,6 +747,7 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
         wave_sync();
     }
     constexpr int MG = col_word0_slots(CPT) / 4;   // groups of word 0
+    col_list_tables<CPT, NG>(C, W, cf);
     const Unlisted U = col_marks<CPT>(C, W, cf);
     const int nx = U.few;
     if (CPT > 0 && U.many) {
@@ -766,7 +767,6 @@ __device__ __forceinline__ void col_decode(const ColPlan& C, const ColWave& W, c
         }
         return;
     }
-    col_list_tables<CPT, NG>(C, W, cf);
     if (nx) col_stage_few<CPT>(C, W, cf, 0, 0u);
     wave_sync();
     const int g0 = min(C.ns, col_word0_slots(CPT));
