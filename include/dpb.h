@@ -153,7 +153,9 @@ dpb_status dpb_encode(const dpb_plan* plan, const void* x, dpb_dtype x_dtype, in
 /* DECODE (§2.1): y = sum_slots coef * phi_idx, directions generated on chip.
  *   idx, coef : device [T, k_tot] (read; any valid code, not only encoder output)
  *   y         : device [T, d], fp32 or bf16 (y_dtype; written)
- * fp32 accumulation; bf16 output rounds to nearest even. */
+ * fp32 accumulation; bf16 output rounds to nearest even.  A coordinate held by
+ * several basis slots gets their sum in slot order, and a token's result does
+ * not depend on the other tokens of the call. */
 dpb_status dpb_decode(const dpb_plan* plan, const int32_t* idx, const float* coef, int64_t T,
                       void* y, dpb_dtype y_dtype, void* stream);
 
@@ -177,7 +179,10 @@ dpb_status dpb_forward(const dpb_plan* plan, const void* x, dpb_dtype x_dtype, i
  *   idx       : device [T, k_tot] int32 (read)
  *   grad_y    : device [T, d], fp32 or bf16 (g_dtype; read)
  *   grad_coef : device [T, k_tot] fp32 (written; 0 on padding slots)
- *   grad_x    : device [T, d], fp32 or bf16 (gx_dtype; written) */
+ *   grad_x    : device [T, d], fp32 or bf16 (gx_dtype; written)
+ * A NaN in a row of g reaches that row's outputs only, and so does an
+ * infinity; in fp32 an infinite g (or one beyond the largest bf16) gives NaN
+ * in the last level's slots whose parent is in the code. */
 dpb_status dpb_decode_bwd(const dpb_plan* plan, const int32_t* idx, const void* grad_y,
                           dpb_dtype g_dtype, int64_t T, float* grad_coef, void* grad_x,
                           dpb_dtype gx_dtype, void* stream);

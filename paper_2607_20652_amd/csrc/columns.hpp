@@ -1,5 +1,6 @@
-// Column decode: y = sum_s coef_s phi_{c_s} of plans whose last level decodes
-// through parent columns, straight from registers to the output rows.
+// Column decode: y = sum_s coef_s phi_{c_s} for codes of at most 254 slots, the
+// last level through parent columns where the plan has them, straight from
+// registers to the output rows.
 //
 // A wave takes TPW = 16 / CPT tokens (CPT parent columns per token, a power
 // of two); each token owns LPT = 64 / TPW lanes, and a lane owns the
@@ -22,9 +23,9 @@
 //    leave each lane the sums of its own coordinates;
 //  * writes the pair.
 // Vector issue and LDS latency bound it.  Nothing of the row goes through LDS,
-// so a wave holds 6.3 KB (train shape, d 768, k 96) instead of 11.5 and the
-// kernels fit 128 registers: four waves per SIMD instead of three, and a
-// quarter fewer vector instructions.  Measured against the row-in-LDS decode
+// so a wave holds 7 KB (d 768, k 96) instead of 11.5 and the kernels are held
+// to 128 registers: four waves per SIMD instead of three, and a quarter fewer
+// vector instructions.  Measured against the row-in-LDS decode
 // it replaced here: 65,536 tokens d 768 k 96: 195 -> 137 us; 16,384 tokens
 // d 1024 k 144: 211 -> 87 us; 8,192 tokens d 768 k 56: 33 -> 19 us; the
 // backward 367 -> 304, 285 -> 191 and 55 -> 37 us.  (Five waves per SIMD
@@ -384,8 +385,8 @@ __device__ __forceinline__ float col_word_sum(uint32_t tb, uint32_t x, float t)
 // vector instructions a slot and step, against a table set-up per pass and
 // one instruction a slot.  Decode of 16,381 tokens d 768 k 96, us, one by one
 // and in passes: 8 slots 55 and 69, 16 slots 67 and 68, 32 slots 84 and 65; at
-// d 4096 k 80 (two waves a CU, where the set-ups' latency shows) 32 slots 685
-// and 785.  Without leaf columns all of them are added one by one: they are
+// d 4096 k 80 (one workgroup a CU, where the set-ups' latency shows) 32 slots
+// 685 and 785.  Without leaf columns all of them are added one by one: they are
 // hashed indices on level 0 alone.
 constexpr int col_few(int cpt) { return cpt ? 16 : 1 << 30; }
 
@@ -482,8 +483,8 @@ constexpr int kColPass = 4;   // coordinate steps of a pass
 // as many words of them at a time as the plan's tables have room for.  The
 // tables are built anew for each pass, the plan's own after them: room for
 // both would take a workgroup a CU from every code.  A code of 64 leaves and
-// no parent, 16,381 tokens d 768, us: decode 254 one by one, 80 here (108 in
-// the row-in-LDS kernels); backward 344, 143 (174).
+// no parent, 16,381 tokens d 768, us: decode 254 one by one, 77 here (108 in
+// the row-in-LDS kernels); backward 344, 139 (174).
 template <int CPT, int NG>
 __device__ __forceinline__ void col_pass(const ColPlan& C, const ColWave& W, const float* cf, Unlisted U, int m0,
                                          float (&ex)[2 * kColPass])

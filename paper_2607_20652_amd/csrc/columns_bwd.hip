@@ -1,4 +1,4 @@
-// Decode-backward of plans that decode through parent columns, for gfx950.
+// Decode-backward of codes of at most 254 slots (columns.hpp), for gfx950.
 #include "columns.hpp"
 
 namespace dpb {
@@ -110,8 +110,7 @@ __device__ __forceinline__ void col_scores(const ColPlan& C, const DevPlan& P, c
     wave_sync();
 }
 
-// The backward of plans that decode through parent columns (P.wave_tokens =
-// 16 / CPT): grad_coef as in decode_bwd2_kernel, then the column decode of it.
+// The backward over columns (P.wave_tokens = col_tpw(CPT)): grad_coef as in decode_bwd2_kernel, then the column decode of it.
 template <int CPT, int NG, bool G_BF16, bool GX_BF16>
 __global__ __launch_bounds__(kColThreads, col_bwd_waves(CPT, G_BF16)) void col_bwd_kernel(ColPlan C, DevPlan P, const int32_t* __restrict__ idx,
                                                                  const void* __restrict__ g, int64_t T,

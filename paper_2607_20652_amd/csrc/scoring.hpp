@@ -27,8 +27,8 @@ struct ActTile {
 
 // Words 4 m, m < MW, of the sign bitmap of index pu (from the table row nt of
 // the first of them), two nibble groups at a time: the XOR of one table row
-// per group (parity is linear in the index bits; table layout [g][w][16]: word w of group g for nibble value v at
-// (g * nchunk + w) * 16 + v).  Every read has a fixed offset from its group's
+// per group (parity is linear in the index bits; table layout [g][w][16]: word
+// w of group g for nibble value v at (g * nchunk + w) * 16 + v).  Every read has a fixed offset from its group's
 // address and each pair of groups folds in one instruction a word.
 template <int MW>
 __device__ __forceinline__ void bitmap_words(const uint32_t* nt, int nchunk, int groups, uint32_t pu, bool live,
